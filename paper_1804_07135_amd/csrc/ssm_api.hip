@@ -106,8 +106,10 @@ struct Plan {
     std::vector<long long> nh_size;   // elements per distinct shape
     std::vector<int> wm_xf[2], wm_xi[2], wm_conv[kConvSlots];  // per kind
     std::vector<int> wm_arc, wm_site, wm_img, wm_sitep, wm_site4;
-    long long n_img = 0, n_spin = 0, n_x = 0, n_nh = 0, n_ep = 0, n_ap = 0, n_fp = 0, n_fm = 0;
-    size_t lds_xf = 0, lds_xi = 0, lds_conv = 0;
+    // n_x, n_xp: complex values of the x half-spectra X and of the convolved
+    // ones X' kept apart from them (problems not convolved in place)
+    long long n_img = 0, n_spin = 0, n_x = 0, n_xp = 0, n_nh = 0, n_ep = 0, n_ap = 0, n_fp = 0, n_fm = 0;
+    size_t lds_xf = 0, lds_xi = 0, lds_conv = 0, lds_conv1[kConvSlots] = {};
     size_t scratch_bytes = 0;
     // workspace offsets
     size_t o_P, o_wm, o_tw, o_tw64, o_s, o_ss, o_h, o_nh, o_big, o_ep, o_ap, o_fp, o_E, o_T,
@@ -141,6 +143,10 @@ size_t lds_xinv(const Prob& p, int yt, size_t tsize)
 
 size_t lds_convg(const Prob& p, int G, size_t tsize)
 {
+    if (p.conv1) {
+        const Conv1Cfg c = conv1_cfg(conv_build(p.mz, p.lmy, p.f3y), (int)tsize);
+        return conv1_lds(c, std::min(G, c.g), (int)tsize);
+    }
     const int n = G * 3 * p.nz * p.my;
     if (conv_ct_shape(p.mz, p.lmy, p.f3y) || conv_ct3_shape(p.mz, p.lmy, p.f3y))
         return (size_t)(2 * p.my + padded_len(n, conv_padl(p.mz, p.lmy, p.f3y, (int)tsize))) * 2 * tsize;
@@ -209,17 +215,19 @@ Tiles default_tiles(const Prob& p, size_t tsize, long long batch_rows, long long
     t.yt = yi;
     const int per = 3 * p.nz * p.ny;
     int gmax = std::max(1, kConvElems / per);
-    while (gmax > 1 && lds_convg(p, gmax, tsize) > kLdsTarget) --gmax;
+    if (p.conv1) gmax = conv1_cfg(conv_build(p.mz, p.lmy, p.f3y), (int)tsize).g;
+    while (!p.conv1 && gmax > 1 && lds_convg(p, gmax, tsize) > kLdsTarget) --gmax;
     // as many slices per workgroup as keep about 1024 workgroups in a
     // launch over the whole batch (small lattices: several wavefronts' line
     // groups per workgroup)
-    t.gconv = (int)std::max<long long>(1, std::min<long long>(gmax, batch_slices / 1024));
+    // (512 where the monolayer kernel's steps share few lanes per slice)
+    t.gconv = (int)std::max<long long>(1, std::min<long long>(gmax, batch_slices / (p.conv1 ? 512 : 1024)));
     return t;
 }
 
 int pad8(int n) { return (n + 7) / 8 * 8; }
 
-void apply_tiles(Prob& p, const Tiles& t)
+void apply_tiles(Prob& p, const Tiles& t, size_t tsize)
 {
     p.ytf = t.ytf;
     p.ntyf = (p.ny + p.ytf - 1) / p.ytf;
@@ -231,10 +239,18 @@ void apply_tiles(Prob& p, const Tiles& t)
     p.wgi = pad8(p.K * p.tiles);
     p.gconv = t.gconv;
     p.xcd_remap = (t.gconv == 1) ? 1 : 0;
+    if (p.conv1) {
+        // at most what the build's LDS holds, and the images of a kx spread
+        // evenly over its workgroups
+        const int g = std::min(t.gconv, conv1_cfg(conv_build(p.mz, p.lmy, p.f3y), (int)tsize).g);
+        const int n = (p.K + g - 1) / g;
+        p.gconv = (p.K + n - 1) / n;
+    }
 }
 
 int conv_wgs(const Prob& p)
 {
+    if (p.conv1) return ((p.mx + 1 + 7) / 8) * 8 * ((p.K + p.gconv - 1) / p.gconv);
     if (p.xcd_remap) return ((p.mx + 1 + 7) / 8) * 8 * p.K;
     const long long slices = (long long)p.K * (p.mx + 1);
     const int w = (int)((slices + p.gconv - 1) / p.gconv);
@@ -256,7 +272,7 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
     pl.P.resize(np);
     pl.geo.resize(np);
     std::map<std::tuple<int, int, int>, int> shape_id;
-    long long img = 0, spin = 0, xo = 0, ep = 0, ap = 0, fp = 0, fm = 0;
+    long long img = 0, spin = 0, xo = 0, xpo = 0, ep = 0, ap = 0, fp = 0, fm = 0;
     long long batch_rows = 0, batch_slices = 0;
     // SSM_LEN3_CT_X / _Y: precisions (bit 0 FP32-mixed, bit 1 FP64) in
     // which a compile-time 3 2^a length is preferred to a compile-time power
@@ -284,8 +300,9 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         p.pz = q.nz > 1 ? 2 * p.mz : 1;
         p.nhz = q.nz > 1 ? 2 : 1;
         p.N = (long long)q.nx * q.ny * q.nz;
+        p.conv1 = conv1_shape(p.mz, p.lmy, p.f3y) ? 1 : 0;
         const Tiles t = tiles ? (*tiles)[i] : default_tiles(p, pl.tsize, batch_rows, batch_slices);
-        apply_tiles(p, t);
+        apply_tiles(p, t, pl.tsize);
         pl.tiles.push_back(t);
         if (lds_xfwd(p, p.ytf, pl.tsize) > kLdsMax || lds_xinv(p, p.yt, pl.tsize) > kLdsMax ||
             lds_convg(p, p.gconv, pl.tsize) > kLdsMax) {
@@ -295,6 +312,7 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         p.img0 = (int)img;
         p.s_off = spin;
         p.x_off = xo;
+        p.xo_off = p.conv1 ? xo : xpo;  // (xpo: completed below, after n_x is known)
         p.ep_off = ep;
         p.ap_off = ap;
         p.arc_chunks = (int)((3 * p.N + kNT * kArcEPT - 1) / (kNT * kArcEPT));
@@ -326,8 +344,10 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         p.J = q.J; p.d = q.d; p.ku = q.ku; p.D = q.dip;
         img += p.K;
         spin += (long long)p.K * 3 * p.N;
-        xo += (long long)p.K * (p.mx + 1) * 3 * p.nz * p.ny;
-        xo = (xo + 31) & ~31LL;  // every problem's spectra start 256-byte aligned (paired 16-byte accesses)
+        // every problem's spectra start 256-byte aligned (paired 16-byte accesses)
+        const long long nxs = ((long long)p.K * (p.mx + 1) * 3 * p.nz * p.ny + 31) & ~31LL;
+        xo += nxs;
+        if (!p.conv1) xpo += nxs;
         // sized for the smallest inverse tile (2 rows) so that retuned tiles
         // keep the workspace layout
         ep += (long long)p.K * p.nz * ((p.ny + 1) / 2) * kNTerm;
@@ -352,8 +372,11 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         pl.red_kinds |= p.red1 ? 2 : 1;
         pl.lds_xf = std::max(pl.lds_xf, lds_xfwd(p, p.ytf, pl.tsize));
         pl.lds_xi = std::max(pl.lds_xi, lds_xinv(p, p.yt, pl.tsize));
-        pl.lds_conv = std::max(pl.lds_conv, lds_convg(p, p.gconv, pl.tsize));
+        size_t& lc = p.conv1 ? pl.lds_conv1[conv_slot(conv_build(p.mz, p.lmy, p.f3y))] : pl.lds_conv;
+        lc = std::max(lc, lds_convg(p, p.gconv, pl.tsize));
     }
+    for (Prob& q : pl.P)
+        if (!q.conv1) q.xo_off += xo;
     // kernel-spectrum offsets per shape
     std::vector<long long> nh_off(pl.shapes.size());
     long long nh = 0;
@@ -362,7 +385,7 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         nh += (pl.nh_size[g] + 63) / 64 * 64;
     }
     for (int i = 0; i < np; ++i) pl.P[i].nh_off = nh_off[pl.geo[i]];
-    pl.n_img = img; pl.n_spin = spin; pl.n_x = xo; pl.n_nh = nh;
+    pl.n_img = img; pl.n_spin = spin; pl.n_x = xo; pl.n_xp = xpo; pl.n_nh = nh;
     for (const Prob& q : pl.P) {
         pl.kmax = std::max(pl.kmax, q.K);
         if (q.K <= 16) pl.kmax_le16 = std::max(pl.kmax_le16, q.K);
@@ -405,7 +428,7 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
     // line of slack after it keeps those reads inside the workspace
     int my_max = 1;
     for (const Prob& q : pl.P) my_max = std::max(my_max, q.my);
-    pl.o_big = take(std::max((size_t)(2 * cs * xo + cs * my_max), pl.scratch_bytes));
+    pl.o_big = take(std::max((size_t)(cs * (xo + xpo) + cs * my_max), pl.scratch_bytes));
     pl.o_ep = take(8 * ep);
     pl.o_ap = take(8 * ap);
     pl.o_fp = take(8 * fp);
@@ -481,6 +504,7 @@ struct ssm_ctx {
         WorkMap w;
         w.start = at<int>(pl.o_wm) + which * (pl.np + 1);
         w.total = v.back();
+        w.lds = 0;
         return w;
     }
     struct XMaps { WorkMap m[2]; };
@@ -490,7 +514,10 @@ struct ssm_ctx {
     ConvMaps wm_conv() const
     {
         ConvMaps r;
-        for (int j = 0; j < kConvSlots; ++j) r.m[j] = wm(4 + j, pl.wm_conv[j]);
+        for (int j = 0; j < kConvSlots; ++j) {
+            r.m[j] = wm(4 + j, pl.wm_conv[j]);
+            r.m[j].lds = pl.lds_conv1[j];
+        }
         return r;
     }
     WorkMap wm_arc() const { return wm(4 + kConvSlots, pl.wm_arc); }
@@ -514,7 +541,6 @@ struct ssm_ctx {
         return r;
     }
     void* X() const { return ws + pl.o_big; }
-    void* Xp() const { return ws + pl.o_big + 2 * pl.tsize * pl.n_x; }
 };
 
 namespace {
@@ -578,12 +604,12 @@ struct Ops {
         });
         if (e != hipSuccess) return e;
         e = timed(c, st, KK_CONV, [&] {
-            return launch_conv<T>(pl.mz, c->P(), pl.np, c->wm_conv().m, c->X(), c->Xp(),
+            return launch_conv<T>(pl.mz, c->P(), pl.np, c->wm_conv().m, c->X(),
                                   c->at<T>(pl.o_nh), tw, done, pl.lds_conv, st);
         });
         if (e != hipSuccess) return e;
         return timed(c, st, KK_XINV, [&] {
-            return launch_xinv<T>(c->P(), pl.np, c->wm_xi().m, c->Xp(), src, s_star, hdst,
+            return launch_xinv<T>(c->P(), pl.np, c->wm_xi().m, c->X(), src, s_star, hdst,
                                   c->at<double>(pl.o_ep), tw, done, mode, tau, fcp, fcd, pl.lds_xi, st);
         });
     }
@@ -934,10 +960,10 @@ double time_kernel(ssm_ctx* c, int kind, int reps)
         if (kind == KK_XFWD)
             e = launch_xfwd<T>(c->P(), pl.np, c->wm_xf().m, s, c->X(), tw, nullptr, pl.lds_xf, c->stream);
         else if (kind == KK_CONV)
-            e = launch_conv<T>(pl.mz, c->P(), pl.np, c->wm_conv().m, c->X(), c->Xp(), c->at<T>(pl.o_nh), tw,
+            e = launch_conv<T>(pl.mz, c->P(), pl.np, c->wm_conv().m, c->X(), c->at<T>(pl.o_nh), tw,
                                nullptr, pl.lds_conv, c->stream);
         else
-            e = launch_xinv<T>(c->P(), pl.np, c->wm_xi().m, c->Xp(), s, nullptr, nullptr,
+            e = launch_xinv<T>(c->P(), pl.np, c->wm_xi().m, c->X(), s, nullptr, nullptr,
                                c->at<double>(pl.o_ep), tw, nullptr, EPI_TERMS, 0.0, 0.0, 1.0, pl.lds_xi,
                                c->stream);
         if (e != hipSuccess || hipEventRecord(b, c->stream) != hipSuccess) return 1e30;
@@ -1146,7 +1172,7 @@ void carve_static(Plan& pl)
     pl.o_tw = take(cs * kTwCompact);
     pl.o_tw64 = take(16 * kTwM);
     pl.o_nh = take(ts * pl.n_nh);
-    pl.o_big = take(std::max((size_t)(2 * cs * pl.n_x + cs * my_max), pl.scratch_bytes));
+    pl.o_big = take(std::max((size_t)(cs * (pl.n_x + pl.n_xp) + cs * my_max), pl.scratch_bytes));
     pl.o_ep = take(8 * pl.n_ep);
     pl.o_flags = take(4);
     pl.total = o;

@@ -52,12 +52,44 @@ __host__ __device__ constexpr bool conv_ct3_shape(int mz, int lmy, int f3y)
 {
     return SSM_CONV_CT && f3y && mz <= 8 && lmy >= 4 && lmy <= 6;
 }
+// monolayers (nz = 1): one kernel (k_conv1) at the same y lengths
+__host__ __device__ constexpr bool conv1_shape(int mz, int lmy, int f3y)
+{
+    return mz == 1 && (conv_ct_shape(mz, lmy, f3y) || conv_ct3_shape(mz, lmy, f3y));
+}
 // build serving a problem: the y length's log2 (5..8) for the compile-time
 // power-of-two builds, 16 + log2 of the power-of-two factor (20..22) for the
 // compile-time 3 2^a builds, 0 for the runtime-length one
 __host__ __device__ constexpr int conv_build(int mz, int lmy, int f3y)
 {
     return conv_ct_shape(mz, lmy, f3y) ? lmy : conv_ct3_shape(mz, lmy, f3y) ? 16 + lmy : 0;
+}
+
+// The monolayer convolution's split of the y length m = A B, by build: a lane
+// transforms A inputs at stride B (A = 12 for lengths 3 2^a) in the first
+// step.  nt threads and at most g slices per workgroup: 3 B g items in the
+// first step, near nt, in an LDS share that leaves three workgroups to a CU
+// (256 and 384: more, of two wavefronts); twlds: the twiddle table has a copy
+// in LDS (0 where that would cost a workgroup).
+struct Conv1Cfg {
+    int A, B, nt, g, twlds;
+};
+__host__ __device__ constexpr Conv1Cfg conv1_cfg(int build, int tsize)
+{
+    return build == 5    ? Conv1Cfg{8, 4, 256, 16, 1}
+           : build == 20 ? Conv1Cfg{12, 4, 256, 10, 1}
+           : build == 6  ? (tsize == 4 ? Conv1Cfg{16, 4, 256, 10, 1} : Conv1Cfg{16, 4, 128, 5, 1})
+           : build == 21 ? (tsize == 4 ? Conv1Cfg{12, 8, 256, 10, 1} : Conv1Cfg{12, 8, 128, 5, 1})
+           : build == 7  ? (tsize == 4 ? Conv1Cfg{16, 8, 256, 8, 1} : Conv1Cfg{16, 8, 128, 4, 0})
+           : build == 22 ? (tsize == 4 ? Conv1Cfg{12, 16, 256, 5, 1} : Conv1Cfg{12, 16, 128, 2, 1})
+                         : (tsize == 4 ? Conv1Cfg{16, 16, 128, 2, 1} : Conv1Cfg{16, 16, 128, 2, 0});
+}
+// LDS elements of one line: B rows of the 2A values of both halves, an odd
+// stride apart (strided writes and contiguous reads both meet distinct banks)
+__host__ __device__ constexpr int conv1_line(Conv1Cfg c) { return c.B * (2 * c.A + 1); }
+__host__ __device__ constexpr size_t conv1_lds(Conv1Cfg c, int G, int tsize)
+{
+    return (size_t)((c.twlds ? 2 * c.A * c.B : 0) + G * 3 * conv1_line(c)) * 2 * tsize;
 }
 
 // LDS layout of the line buffers (pad_for, padx in ssm_fft.hpp).  The
@@ -124,12 +156,16 @@ struct Prob {
     int ytf, ntyf, tilesf; // the same for the forward x kernel
     int wgf, wgi;          // forward / inverse x workgroups (K * tiles, padded to 8)
     int img0;              // index of this problem's first image in batch-wide arrays
-    int gconv;             // consecutive (image, kx) slices per convolution workgroup
+    int gconv;             // (image, kx) slices per convolution workgroup: consecutive ones (kx fastest),
+                           // or images of one kx (monolayers)
+    int conv1;             // 1: convolution by k_conv1
     int arc_chunks;        // arc-length workgroups (flat chunks of 3N) per image
     int xcd_remap;         // convolution kernel: group same-kx slices on one XCD
     long long N;           // sites per image
     long long s_off;       // element offset of image 0 in spin / field buffers
-    long long x_off;       // complex-element offset in the x-spectrum buffers
+    long long x_off;       // complex-element offset in the x-spectrum buffer X
+    long long xo_off;      // offset of the convolved spectra from the same base: x_off where the
+                           // convolution works in place (monolayers), in X' after X otherwise
     long long nh_off;      // element offset of this shape's dipole-kernel spectrum
     long long ep_off;      // offset (doubles) of energy partials: [K][tiles][kNTerm]
     long long ap_off;      // offset (doubles) of arc partials: [K][arc_chunks*4]
@@ -149,6 +185,7 @@ struct Prob {
 struct WorkMap {
     int* start;      // device: [nprob + 1] prefix sums of workgroup counts
     int total;
+    size_t lds;      // dynamic LDS bytes (monolayer convolution builds)
 };
 
 // ------------------------------------------------------------------------
@@ -164,11 +201,10 @@ __host__ __device__ constexpr int conv_slot(int b) { return b == 0 ? 0 : (b <= 8
 template <typename T>
 hipError_t launch_xfwd(const Prob* P, int np, const WorkMap* wm, const T* s, void* X,
                        const void* tw, const int* done, size_t lds, hipStream_t st);
-// X' receives the convolved x half-spectra (X keeps the inputs)
+// the convolved x half-spectra go to Prob::xo_off of the same buffer
 template <typename T>
-hipError_t launch_conv(int mz, const Prob* P, int np, const WorkMap* wm, void* X,
-                       void* Xp, const T* nhat, const void* tw, const int* done, size_t lds,
-                       hipStream_t st);
+hipError_t launch_conv(int mz, const Prob* P, int np, const WorkMap* wm, void* X, const T* nhat, const void* tw,
+                       const int* done, size_t lds, hipStream_t st);
 // mode bits for the inverse/epilogue kernel: EPI_STEP writes the stepped
 // string, EPI_FIELD the field h, EPI_FORCE the damping right-hand side
 // (s.s) h - (s.h) s in place of h, EPI_TERMS the four term partials

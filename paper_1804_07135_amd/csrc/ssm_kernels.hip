@@ -615,7 +615,7 @@ __device__ __forceinline__ void conv_zphase(const Prob& p, int G, int kx0, int h
 // which reads every line of a column, needs workgroup barriers.
 template <typename T, int MZ, int LMY>
 __device__ __forceinline__ void conv_body_ct(const Prob& p, int s0, int G, cplx<T>* __restrict__ X,
-                                             cplx<T>* __restrict__ Xp, const T* __restrict__ nhat,
+                                             const T* __restrict__ nhat,
                                              const cplx<T>* __restrict__ tw, cplx<T>* smem)
 {
     using V = cplx<T>;
@@ -641,7 +641,7 @@ __device__ __forceinline__ void conv_body_ct(const Prob& p, int s0, int G, cplx<
     const V* twl = smem;
     V* lines = smem + 2 * MY;
     V* in = X + p.x_off + (long long)s0 * per;
-    V* out = Xp + p.x_off + (long long)s0 * per;
+    V* out = X + p.xo_off + (long long)s0 * per;
     const int kx0 = s0 % nsl_img;
     const int wave = threadIdx.x >> 6;
     constexpr int NW = kNT / 64;
@@ -753,7 +753,7 @@ __device__ __forceinline__ void conv_body_ct(const Prob& p, int s0, int G, cplx<
 constexpr int kConvU = 4;
 template <typename T, int MZ>
 __device__ __forceinline__ void conv_body(const Prob& p, int s0, int G, cplx<T>* __restrict__ X,
-                                          cplx<T>* __restrict__ Xp, const T* __restrict__ nhat,
+                                          const T* __restrict__ nhat,
                                           const cplx<T>* __restrict__ tw, cplx<T>* smem)
 {
     using V = cplx<T>;
@@ -765,7 +765,7 @@ __device__ __forceinline__ void conv_body(const Prob& p, int s0, int G, cplx<T>*
     V* lines = twl + 2 * my;
     load_twiddles(twl, lmy, f3y, tw);
     V* in = X + p.x_off + (long long)s0 * per;
-    V* out = Xp + p.x_off + (long long)s0 * per;
+    V* out = X + p.xo_off + (long long)s0 * per;
     const int dy = kNT % ny, dr = kNT / ny;
     const int yb = threadIdx.x % ny, rb = threadIdx.x / ny;
     const int kx0 = s0 % nsl_img;
@@ -908,7 +908,7 @@ __device__ __forceinline__ void conv_body(const Prob& p, int s0, int G, cplx<T>*
 // z-phase needs workgroup barriers.
 template <typename T, int MZ, int LMY>
 __device__ __forceinline__ void conv_body_ct3(const Prob& p, int s0, int G, cplx<T>* __restrict__ X,
-                                              cplx<T>* __restrict__ Xp, const T* __restrict__ nhat,
+                                              const T* __restrict__ nhat,
                                               const cplx<T>* __restrict__ tw, cplx<T>* smem)
 {
     using V = cplx<T>;
@@ -927,7 +927,7 @@ __device__ __forceinline__ void conv_body_ct3(const Prob& p, int s0, int G, cplx
     const V* twl = smem;
     V* lines = smem + 2 * MY;
     V* in = X + p.x_off + (long long)s0 * per;
-    V* out = Xp + p.x_off + (long long)s0 * per;
+    V* out = X + p.xo_off + (long long)s0 * per;
     const int kx0 = s0 % nsl_img;
     const int wave = threadIdx.x >> 6;
     constexpr int NW = kNT / 64;
@@ -1049,8 +1049,7 @@ __device__ __forceinline__ void conv_body_ct3(const Prob& p, int s0, int G, cplx
 template <typename T, int MZ, int BUILD>
 __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && MZ <= 8 ? SSM_CONV_WAVES_F32 : 1, 8))) void k_conv(const Prob* __restrict__ P, int np,
                                               const int* __restrict__ wstart,
-                                              cplx<T>* __restrict__ X,
-                                              cplx<T>* __restrict__ Xp, const T* __restrict__ nhat,
+                                              cplx<T>* __restrict__ X, const T* __restrict__ nhat,
                                               const cplx<T>* __restrict__ tw,
                                               const int* __restrict__ done)
 {
@@ -1081,9 +1080,302 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
         G = min(p.gconv, nsl - s0);
     }
     cplx<T>* sm = reinterpret_cast<cplx<T>*>(smem_);
-    if constexpr (BUILD >= 16) conv_body_ct3<T, MZ, BUILD - 16>(p, s0, G, X, Xp, nhat, tw, sm);
-    else if constexpr (BUILD > 0) conv_body_ct<T, MZ, BUILD>(p, s0, G, X, Xp, nhat, tw, sm);
-    else conv_body<T, MZ>(p, s0, G, X, Xp, nhat, tw, sm);
+    if constexpr (BUILD >= 16) conv_body_ct3<T, MZ, BUILD - 16>(p, s0, G, X, nhat, tw, sm);
+    else if constexpr (BUILD > 0) conv_body_ct<T, MZ, BUILD>(p, s0, G, X, nhat, tw, sm);
+    else conv_body<T, MZ>(p, s0, G, X, nhat, tw, sm);
+}
+
+// ---------------------------------------------------------------------------
+// k_conv1: the convolution of monolayers (nz = 1), in place, for G images of
+// one kx.  Both halves hy of the padded y transform run together in three
+// steps, each a few values in the registers of a lane, with one LDS exchange
+// between two steps:
+//   1. A inputs at stride B of a line from global memory, as they are (hy = 0)
+//      and twiddled by W^y (hy = 1): the first pass of the two transforms;
+//   2. for one slice and half, the second pass of all three components at the
+//      frequencies whose values the inverse transform's first pass takes, the
+//      product with the kernel spectrum (xz and yz vanish in a monolayer, so z
+//      is independent of x and y) and that first inverse pass;
+//   3. the last inverse pass of both halves, the second un-twiddled and added
+//      to the first, to global memory.
+// m = 2^a = A B: radix-A and radix-B passes (step 2 takes A / B radix-B
+// transforms and one radix-A inverse transform per component).  m = 3 M:
+// A = 12 is the radix-3 step with the radix-4 pass of the three sub-lines, B =
+// M / 4 the radix of their other pass.  Operations and their order are those
+// of the multi-layer bodies, so a monolayer's results don't depend on which
+// of them ran.
+// The multi-layer bodies with one layer took each half by itself, through
+// five LDS round trips and workgroup barriers, reading X twice and reading
+// back and adding to X'.  Measured (us a launch, FP32 unless said): 64
+// lattices of 48..96 sites, 16 images, 272 -> 121; 112 x 112, 60 images, 39 ->
+// 21 and 240 images 113 -> 56 (FP64: 320 -> 118); 32 x 32, 10 images, FP64,
+// 12.5 -> 6.7.  What bounds it now is vector arithmetic and LDS in about
+// equal parts; its traffic (X once each way) runs at 2.5 TB/s.
+// LDS: (twiddles W_{2m}) + 3 G lines of B rows of 2A (+1) values.
+// ---------------------------------------------------------------------------
+template <typename T, int BUILD>
+__global__ __launch_bounds__(conv1_cfg(BUILD, sizeof(T)).nt)
+    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && BUILD != 8 ? 3 : 2, 8))) void k_conv1(const Prob* __restrict__ P, int np,
+                                                                               const int* __restrict__ wstart,
+                                                                               cplx<T>* __restrict__ X,
+                                                                               const T* __restrict__ nhat,
+                                                                               const cplx<T>* __restrict__ tw,
+                                                                               const int* __restrict__ done)
+{
+    using V = cplx<T>;
+    constexpr Conv1Cfg C = conv1_cfg(BUILD, sizeof(T));
+    constexpr int A = C.A, B = C.B, NT = C.nt, MY = A * B, JS = 2 * A + 1, LS = conv1_line(C);
+    constexpr int F3 = BUILD >= 16, LMY = F3 ? BUILD - 16 : BUILD;
+    static_assert(MY == (F3 ? 3 << LMY : 1 << LMY) && (!F3 || A == 12), "split does not match the length");
+    extern __shared__ double2 smem_[];
+    const int pi = find_problem(wstart, np, blockIdx.x);
+    if (done && done[pi]) return;
+    const Prob& p = P[pi];
+    const int w = blockIdx.x - wstart[pi];
+    // workgroup w: kx = 8 (j / nwk) + w % 8, image group j % nwk (j = w / 8):
+    // the image groups of one kx run back to back on one XCD, whose L2 then
+    // holds that kx's kernel spectrum
+    const int nwk = (p.K + p.gconv - 1) / p.gconv;
+    const int kx = ((w >> 3) / nwk) * 8 + (w & 7), img0 = ((w >> 3) % nwk) * p.gconv;
+    if (kx > p.mx) return;
+    const int G = min(p.gconv, p.K - img0);
+    const int ny = p.ny, m1 = p.mx + 1;
+    V* lines = reinterpret_cast<V*>(smem_) + (C.twlds ? 2 * MY : 0);
+    const V* const twl = C.twlds ? reinterpret_cast<const V*>(smem_) : tw + tw_off(LMY, F3);
+    // the slices of consecutive images are m1 * 3 * ny apart
+    V* const x0 = X + p.x_off + ((long long)img0 * m1 + kx) * 3 * ny;
+    const long long istr = (long long)m1 * 3 * ny;
+    // step 2's item (slice g, half hy, q).  F3: q = 3 k + t < 12 is output k
+    // of sub-line t, and its R = B values give frequencies 12 r + q; else q <
+    // B, the R = A values are frequencies q + B r, and the upper half of the
+    // threads takes the z components, the lower half x and y.
+    constexpr int R = F3 ? B : A, Q = F3 ? 12 : B, NT2 = F3 ? NT : NT / 2;
+    static_assert(C.g * 3 * B <= NT && C.g * 2 * Q <= NT2, "steps 1 and 2 take one item per thread");
+    const bool zpart = !F3 && (int)threadIdx.x >= NT2;
+    const int it2 = (int)threadIdx.x - (zpart ? NT2 : 0);
+    // (threads past the last item load the last one's values and store none)
+    const int n2 = G * 2 * Q;
+    const int gh2 = min(it2, n2 - 1) / Q, q2 = min(it2, n2 - 1) - gh2 * Q;
+    const T* const nh = nhat + p.nh_off + (((long long)kx * 2 + (gh2 & 1)) * 6) * MY + q2;
+    // its kernel-spectrum values, loaded here with step 1's inputs in FP32
+    // (FP64 has no registers to hold them meanwhile)
+    constexpr bool kEarly = sizeof(T) == 4;
+    struct NH {
+        T a[R], xy[R], yy[R], zz[F3 ? R : 1];  // a: xx, or zz where the thread takes z
+    };
+    auto load_nhat = [&](NH& n) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) n.a[r] = nh[Q * r + (zpart ? 5 * MY : 0)];
+        if (!zpart) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                n.xy[r] = nh[Q * r + MY];
+                n.yy[r] = nh[Q * r + 3 * MY];
+                if constexpr (F3) n.zz[r] = nh[Q * r + 5 * MY];
+            }
+        }
+    };
+    NH n;
+    if constexpr (kEarly) load_nhat(n);
+
+    // step 1: item (line, j), inputs j + B a; F3: y = j + B (r + 4 t).  All
+    // loads of the first step are issued before anything waits on them.
+    const int line1 = min((int)threadIdx.x, G * 3 * B - 1) / B, j1 = threadIdx.x & (B - 1), g1 = line1 / 3;
+    V e[A], o[A];
+    {
+        const V* src = x0 + g1 * istr + (line1 - 3 * g1) * ny;
+#pragma unroll
+        for (int a = 0; a < A; ++a) e[a] = src[min(j1 + B * a, ny - 1)];
+    }
+    if constexpr (C.twlds) {
+        load_twiddles(reinterpret_cast<V*>(smem_), LMY, F3, tw);
+        __syncthreads();
+    }
+    if ((int)threadIdx.x < G * 3 * B) {
+        const int line = line1, j = j1;
+        V* dst = lines + line * LS + j * JS;
+        if constexpr (F3) {
+#pragma unroll
+            for (int a = 0; a < A; ++a) {
+                o[a] = cmul_set(e[a], twl[j + B * a]);
+                if (j + B * a >= ny) e[a] = o[a] = mk<V>(0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const V w1 = twl[2 * (j + B * r)], w2 = twl[4 * (j + B * r)];
+                radix3_set<false>(e[r], e[r + 4], e[r + 8], w1, w2);
+                radix3_set<false>(o[r], o[r + 4], o[r + 8], w1, w2);
+            }
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                V u[4], v[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) { u[r] = e[4 * t + r]; v[r] = o[4 * t + r]; }
+                dft_reg<V, 4, false>(u);
+                dft_reg<V, 4, false>(v);
+                // sub-line t, output k: column 3 k + t
+#pragma unroll
+                for (int k = 0; k < 4; ++k) { dst[3 * k + t] = u[k]; dst[A + 3 * k + t] = v[k]; }
+            }
+        } else {
+#pragma unroll
+            for (int a = 0; a < A; ++a) {
+                if (j + B * a >= ny) e[a] = mk<V>(0, 0);
+                o[a] = cmul_set(e[a], twl[j + B * a]);
+            }
+            dft_reg<V, A, false>(e);
+            dft_reg<V, A, false>(o);
+#pragma unroll
+            for (int a = 0; a < A; ++a) { dst[a] = e[a]; dst[A + a] = o[a]; }
+        }
+    }
+    __syncthreads();
+
+    // step 2
+    if (it2 < n2) {
+        // F3: twiddle of value j of a transform at output q / 3 of the first
+        // pass
+        V tw1[F3 ? B : 1];
+        if constexpr (F3) {
+            const int k = q2 / 3;
+#pragma unroll
+            for (int j = 1; j < B; ++j) tw1[j] = twl[6 * j * k];
+        }
+        V* const lg = lines + (gh2 >> 1) * 3 * LS + (gh2 & 1) * A;
+        auto forward = [&](int c, V (&v)[R]) {
+            const V* col = lg + c * LS;
+            if constexpr (F3) {
+#pragma unroll
+                for (int j = 0; j < B; ++j) {
+                    v[j] = col[j * JS + q2];
+                    if (j) v[j] = cmul_set(v[j], tw1[j]);
+                }
+                dft_reg<V, B, false>(v);
+            } else {
+                // A / B radix-B transforms at k = q + B i: frequencies k + A r
+#pragma unroll
+                for (int i = 0; i < A / B; ++i) {
+                    const int k = q2 + B * i;
+                    V u[B];
+#pragma unroll
+                    for (int j = 0; j < B; ++j) {
+                        u[j] = col[j * JS + k];
+                        if (j) u[j] = cmul_set(u[j], twl[2 * j * k]);
+                    }
+                    dft_reg<V, B, false>(u);
+#pragma unroll
+                    for (int r = 0; r < B; ++r) v[i + (A / B) * r] = u[r];
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) settle(v[r]);
+        };
+        // F3: rows r of the same column; else row q, columns 0..A-1.  (The
+        // lanes of one slice and half lie in one wavefront, which reads all
+        // of a component before it writes it.)
+        auto inverse = [&](int c, V (&v)[R]) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) settle(v[r]);
+            dft_reg<V, R, true>(v);
+            V* col = lg + c * LS;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if constexpr (F3) col[r * JS + q2] = v[r];
+                else col[q2 * JS + r] = v[r];
+            }
+        };
+        V x[R];
+        forward(zpart ? 2 : 0, x);
+        if (zpart) {
+            if constexpr (!kEarly) load_nhat(n);
+#pragma unroll
+            for (int r = 0; r < R; ++r) x[r] = mk<V>(n.a[r] * x[r].x, n.a[r] * x[r].y);
+        } else {
+            V y[R];
+            forward(1, y);
+            if constexpr (!kEarly) load_nhat(n);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const V sx = x[r], sy = y[r];
+                x[r] = mk<V>(fma(n.a[r], sx.x, n.xy[r] * sy.x), fma(n.a[r], sx.y, n.xy[r] * sy.y));
+                y[r] = mk<V>(fma(n.xy[r], sx.x, n.yy[r] * sy.x), fma(n.xy[r], sx.y, n.yy[r] * sy.y));
+            }
+            wave_sync();
+            inverse(1, y);
+        }
+        wave_sync();
+        inverse(zpart ? 2 : 0, x);
+        if constexpr (F3) {
+            forward(2, x);
+#pragma unroll
+            for (int r = 0; r < R; ++r) x[r] = mk<V>(n.zz[r] * x[r].x, n.zz[r] * x[r].y);
+            wave_sync();
+            inverse(2, x);
+        }
+    }
+    __syncthreads();
+
+    // step 3, onto the slice.  F3: item (line, j), y = j + B (r + 4 t) from
+    // row j; else item (line, k), y = k + A r from column k.
+    constexpr int N3 = F3 ? B : A;
+    for (int it = threadIdx.x; it < G * 3 * N3; it += NT) {
+        const int line = it / N3, j = it & (N3 - 1), g = line / 3;
+        V* dst = x0 + g * istr + (line - 3 * g) * ny;
+        if constexpr (F3) {
+            const V* src = lines + line * LS + j * JS;
+            V v[2][3][4];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        V a = src[h * A + 3 * r + t];
+                        if (r > 0) a = cmulc_alt(a, twl[6 * r * j]);
+                        v[h][t][r] = a;
+                    }
+                    dft_reg<V, 4, true>(v[h][t]);
+                }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const V w1 = twl[2 * (j + B * r)], w2 = twl[4 * (j + B * r)];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    radix3_set<true>(v[h][0][r], v[h][1][r], v[h][2][r], w1, w2);
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) settle(v[h][t][r]);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int y = j + B * (r + 4 * t);
+                    const V s = cadd(cmulc_set(v[1][t][r], twl[y]), v[0][t][r]);
+                    if (y < ny) dst[y] = s;
+                }
+        } else {
+            const V* src = lines + line * LS + j;
+            V v[2][B];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int r = 0; r < B; ++r) {
+                    v[h][r] = src[r * JS + h * A];
+                    if (r) v[h][r] = cmulc_set(v[h][r], twl[2 * r * j]);
+                }
+                dft_reg<V, B, true>(v[h]);
+#pragma unroll
+                for (int r = 0; r < B; ++r) settle(v[h][r]);
+            }
+#pragma unroll
+            for (int r = 0; r < B; ++r) {
+                const int y = j + A * r;
+                const V s = cadd(cmulc_set(v[1][r], twl[y]), v[0][r]);
+                if (y < ny) dst[y] = s;
+            }
+        }
+    }
 }
 
 // The value of the next (previous) lane of the wavefront: DPP wavefront
@@ -1247,7 +1539,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     // the convolved x half-spectra of the image
     // (as a uniform base and 32-bit byte offsets: an image's spectra span
     // at most 1025 * 3 * 16 * 1024 complex values, under 2^32 bytes)
-    const char* const Xi = reinterpret_cast<const char*>(Xp + p.x_off + (long long)img * (m + 1) * 3 * nz * ny);
+    const char* const Xi = reinterpret_cast<const char*>(Xp + p.xo_off + (long long)img * (m + 1) * 3 * nz * ny);
     __syncthreads();
 #pragma unroll 1
     for (int c = 0; c < 3; ++c) {
@@ -2369,46 +2661,48 @@ hipError_t launch_xfwd(const Prob* P, int np, const WorkMap* wm, const T* s, voi
 }
 
 template <typename T, int MZ, int BUILD>
-static void launch_conv_b(const Prob* P, int np, const WorkMap* wm, cplx<T>* x, cplx<T>* xp,
-                          const T* nhat, const cplx<T>* t, const int* done, size_t lds, hipStream_t st)
+static void launch_conv_b(const Prob* P, int np, const WorkMap* wm, cplx<T>* x, const T* nhat, const cplx<T>* t,
+                          const int* done, size_t lds, hipStream_t st)
 {
     const WorkMap& w = wm[conv_slot(BUILD)];
-    if (w.total)
-        hipLaunchKernelGGL((k_conv<T, MZ, BUILD>), dim3(w.total), dim3(kNT), lds, st, P, np, w.start, x, xp,
-                           nhat, t, done);
+    if (!w.total) return;
+    if constexpr (MZ == 1 && BUILD > 0)
+        hipLaunchKernelGGL((k_conv1<T, BUILD>), dim3(w.total), dim3(conv1_cfg(BUILD, sizeof(T)).nt), w.lds, st, P, np,
+                           w.start, x, nhat, t, done);
+    else
+        hipLaunchKernelGGL((k_conv<T, MZ, BUILD>), dim3(w.total), dim3(kNT), lds, st, P, np, w.start, x, nhat, t,
+                           done);
 }
 
 template <typename T, int MZ>
-static hipError_t launch_conv_mz(const Prob* P, int np, const WorkMap* wm, cplx<T>* x,
-                                 cplx<T>* xp, const T* nhat, const cplx<T>* t, const int* done, size_t lds,
-                                 hipStream_t st)
+static hipError_t launch_conv_mz(const Prob* P, int np, const WorkMap* wm, cplx<T>* x, const T* nhat,
+                                 const cplx<T>* t, const int* done, size_t lds, hipStream_t st)
 {
-    launch_conv_b<T, MZ, 0>(P, np, wm, x, xp, nhat, t, done, lds, st);
+    launch_conv_b<T, MZ, 0>(P, np, wm, x, nhat, t, done, lds, st);
     if constexpr (MZ <= 8 && SSM_CONV_CT) {
-        launch_conv_b<T, MZ, 5>(P, np, wm, x, xp, nhat, t, done, lds, st);
-        launch_conv_b<T, MZ, 6>(P, np, wm, x, xp, nhat, t, done, lds, st);
-        launch_conv_b<T, MZ, 7>(P, np, wm, x, xp, nhat, t, done, lds, st);
-        launch_conv_b<T, MZ, 8>(P, np, wm, x, xp, nhat, t, done, lds, st);
-        launch_conv_b<T, MZ, 20>(P, np, wm, x, xp, nhat, t, done, lds, st);
-        launch_conv_b<T, MZ, 21>(P, np, wm, x, xp, nhat, t, done, lds, st);
-        launch_conv_b<T, MZ, 22>(P, np, wm, x, xp, nhat, t, done, lds, st);
+        launch_conv_b<T, MZ, 5>(P, np, wm, x, nhat, t, done, lds, st);
+        launch_conv_b<T, MZ, 6>(P, np, wm, x, nhat, t, done, lds, st);
+        launch_conv_b<T, MZ, 7>(P, np, wm, x, nhat, t, done, lds, st);
+        launch_conv_b<T, MZ, 8>(P, np, wm, x, nhat, t, done, lds, st);
+        launch_conv_b<T, MZ, 20>(P, np, wm, x, nhat, t, done, lds, st);
+        launch_conv_b<T, MZ, 21>(P, np, wm, x, nhat, t, done, lds, st);
+        launch_conv_b<T, MZ, 22>(P, np, wm, x, nhat, t, done, lds, st);
     }
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_conv(int mz, const Prob* P, int np, const WorkMap* wm, void* X, void* Xp,
-                       const T* nhat, const void* tw, const int* done, size_t lds, hipStream_t st)
+hipError_t launch_conv(int mz, const Prob* P, int np, const WorkMap* wm, void* X, const T* nhat, const void* tw,
+                       const int* done, size_t lds, hipStream_t st)
 {
     cplx<T>* x = (cplx<T>*)X;
-    cplx<T>* xp = (cplx<T>*)Xp;
     const cplx<T>* t = (const cplx<T>*)tw;
     switch (mz) {
-    case 1: return launch_conv_mz<T, 1>(P, np, wm, x, xp, nhat, t, done, lds, st);
-    case 2: return launch_conv_mz<T, 2>(P, np, wm, x, xp, nhat, t, done, lds, st);
-    case 4: return launch_conv_mz<T, 4>(P, np, wm, x, xp, nhat, t, done, lds, st);
-    case 8: return launch_conv_mz<T, 8>(P, np, wm, x, xp, nhat, t, done, lds, st);
-    case 16: return launch_conv_mz<T, 16>(P, np, wm, x, xp, nhat, t, done, lds, st);
+    case 1: return launch_conv_mz<T, 1>(P, np, wm, x, nhat, t, done, lds, st);
+    case 2: return launch_conv_mz<T, 2>(P, np, wm, x, nhat, t, done, lds, st);
+    case 4: return launch_conv_mz<T, 4>(P, np, wm, x, nhat, t, done, lds, st);
+    case 8: return launch_conv_mz<T, 8>(P, np, wm, x, nhat, t, done, lds, st);
+    case 16: return launch_conv_mz<T, 16>(P, np, wm, x, nhat, t, done, lds, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -3219,8 +3513,8 @@ hipError_t launch_fill_double(double* p, int n, double v, hipStream_t st)
 #define SSM_INST(T)                                                                                \
     template hipError_t launch_xfwd<T>(const Prob*, int, const WorkMap*, const T*, void*,         \
                                        const void*, const int*, size_t, hipStream_t);             \
-    template hipError_t launch_conv<T>(int, const Prob*, int, const WorkMap*, void*, void*,            \
-                                       const T*, const void*, const int*, size_t, hipStream_t);   \
+    template hipError_t launch_conv<T>(int, const Prob*, int, const WorkMap*, void*, const T*,    \
+                                       const void*, const int*, size_t, hipStream_t);             \
     template hipError_t launch_xinv<T>(const Prob*, int, const WorkMap*, const void*,              \
                                        const T*,                                                    \
                                        T*, T*, double*, const void*, const int*, int, double,     \
