@@ -205,8 +205,8 @@ Tiles default_tiles(const Prob& p, size_t tsize, long long batch_rows, long long
     yf = std::min(yf, ycap);
     while (yf > 2 && lds_xfwd(p, yf, tsize) > kLdsTarget) yf /= 2;
     // small batches: more, shorter tiles (down to 64-byte runs) until a
-    // launch has about four workgroups per CU
-    while (yf * cs > 64 && batch_rows / yf < 1024) yf /= 2;
+    // launch has about four workgroups (one per component) per CU
+    while (yf * cs > 64 && 3 * batch_rows / yf < 1024) yf /= 2;
     t.ytf = yf;
     int yi = std::max(2, 128 / cs);
     while (yi * p.mx < 4096 && yi < ycap && lds_xinv(p, 2 * yi, tsize) <= kLdsTarget) yi *= 2;
@@ -232,7 +232,7 @@ void apply_tiles(Prob& p, const Tiles& t, size_t tsize)
     p.ytf = t.ytf;
     p.ntyf = (p.ny + p.ytf - 1) / p.ytf;
     p.tilesf = p.nz * p.ntyf;
-    p.wgf = pad8(p.K * p.tilesf);
+    p.wgf = pad8((p.csplit ? 3 : 1) * p.K * p.tilesf);
     p.yt = t.yt;
     p.nty = (p.ny + p.yt - 1) / p.yt;
     p.tiles = p.nz * p.nty;
@@ -301,6 +301,13 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         p.nhz = q.nz > 1 ? 2 : 1;
         p.N = (long long)q.nx * q.ny * q.nz;
         p.conv1 = conv1_shape(p.mz, p.lmy, p.f3y) ? 1 : 0;
+        // one component per forward x workgroup until a launch has 4096
+        // tiles (of about 4096 elements) without it: shorter chains and more
+        // workgroups (64 x 64, 20 images, FP32: 11.0 -> 7.8 us; 64 lattices
+        // of 72 x 72, 16 images: 76 -> 68; 200 x 180 x 5, 20 images: 50 ->
+        // 45); beyond that the twiddle loads and barriers it repeats cost
+        // more (256 x 256 x 8, 48 images: 181 -> 189, FP64 390 -> 415)
+        p.csplit = batch_rows * p.mx < (1 << 24) ? 1 : 0;
         const Tiles t = tiles ? (*tiles)[i] : default_tiles(p, pl.tsize, batch_rows, batch_slices);
         apply_tiles(p, t, pl.tsize);
         pl.tiles.push_back(t);

@@ -154,7 +154,8 @@ struct Prob {
     int nty;               // ceil(ny / yt)
     int tiles;             // inverse-x tiles per image = nz * nty (energy partials)
     int ytf, ntyf, tilesf; // the same for the forward x kernel
-    int wgf, wgi;          // forward / inverse x workgroups (K * tiles, padded to 8)
+    int wgf, wgi;          // forward / inverse x workgroups (K * tiles, forward times 3 with csplit; padded to 8)
+    int csplit;            // 1: a forward x workgroup takes one component of its tile, else all three
     int img0;              // index of this problem's first image in batch-wide arrays
     int gconv;             // (image, kx) slices per convolution workgroup: consecutive ones (kx fastest),
                            // or images of one kx (monolayers)

@@ -124,6 +124,27 @@ __device__ __forceinline__ int find_problem(const int* __restrict__ start, int n
     return find_problem_lane(start, np, b);
 }
 
+// Problem pi, its first workgroup w0 and whether its work is off (done).  A
+// value from each cache line of the descriptor is loaded together with the
+// two others, ahead of the branch on done, so that a kernel starts after one
+// memory latency instead of three in a row (the fields it uses later then
+// come from the scalar cache).  With the kernel arguments preloaded into
+// registers (a build flag) and Prob::csplit: 64 x 64, 20 images, FP32 2.04 ->
+// 1.85 ms per 40 iterations; 32 x 32, 10 images, FP64 1.60 -> 1.45 ms.
+__device__ __forceinline__ const Prob& problem(const Prob* __restrict__ P, int pi, const int* __restrict__ wstart,
+                                               const int* __restrict__ done, int& w0, bool& off)
+{
+    const Prob& p = P[pi];
+    const int d = done ? done[pi] : 0;
+    w0 = wstart[pi];
+    const int a = p.nx, b = p.tiles, c = p.ichunks;
+    const long long n = p.N, s = p.nh_off;
+    const double j = p.J;
+    asm volatile("" ::"s"(d), "s"(w0), "s"(a), "s"(b), "s"(c), "s"(n), "s"(s), "s"(j));
+    off = d != 0;
+    return p;
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own
 // L2).  Give each XCD a contiguous run of work items so that neighbouring
 // items (adjacent rows, shared halo) are processed by one L2 back to back.
@@ -392,8 +413,8 @@ __device__ __forceinline__ void xfwd_load3(const T* __restrict__ sc, cplx<T>* li
 
 // ---------------------------------------------------------------------------
 // k_xfwd: rows of a tile (image, z, ytf rows) -> x half-spectra, one spin
-// component at a time.  Two real rows of one component form one complex
-// signal a + i b; its length-2m spectrum Z gives A(k) = (Z(k) + conj Z(-k))/2
+// component at a time, or (Prob::csplit) one component per workgroup.  Two
+// real rows of one component form one complex signal a + i b; its length-2m spectrum Z gives A(k) = (Z(k) + conj Z(-k))/2
 // and B(k) = -i (Z(k) - conj Z(-k))/2 for k = 0..m.
 // Output layout X[img][kx][c][z][y]: a tile writes ytf consecutive y values.
 // LDS: twiddles (2m) + ytf lines of m (padded layout).
@@ -410,13 +431,18 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     using V = cplx<T>;
     extern __shared__ double2 smem_[];
     const int pi = find_problem(wstart, np, blockIdx.x);
-    if (done && done[pi]) return;
-    const Prob& p = P[pi];
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
     if (p.f3x != F3) return;  // served by the other length kind's launch
-    const int t = xcd_item(blockIdx.x - wstart[pi], p.wgf);
-    if (t >= p.K * p.tilesf) return;
+    const int t = xcd_item(blockIdx.x - w0, p.wgf);
+    // the workgroup's components: all three, or (split) one
+    const int nwc = p.csplit ? 3 : 1;
+    if (t >= nwc * p.K * p.tilesf) return;
     const int ty = t % p.ntyf, rest = t / p.ntyf;
-    const int z = rest % p.nz, img = rest / p.nz;
+    const int z = rest % p.nz, ic = rest / p.nz, img = ic / nwc, c0 = p.csplit ? ic - 3 * img : 0;
+    const int c1 = p.csplit ? c0 + 1 : 3;
     const int yt = p.ytf, hp = yt >> 1, nx = p.nx, ny = p.ny, nz = p.nz, m = p.mx, lm = p.lmx;
     constexpr int f3 = F3;
     const int lhp = __ffs(hp) - 1;  // tiles are powers of two
@@ -438,7 +464,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     constexpr int VW = 16 / sizeof(T);
     const bool vecw = !(nx & (VW - 1)) && !(reinterpret_cast<size_t>(si) & 15);
 #pragma unroll 1
-    for (int c = 0; c < 3; ++c) {
+    for (int c = c0; c < c1; ++c) {
         const T* sc = si + (long long)c * N;
         if constexpr (F3) {
             xfwd_load3<T>(sc, lines, twl, vecw, hp, lm, y0, nx, ny, psh);
@@ -1055,10 +1081,12 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 {
     extern __shared__ double2 smem_[];
     const int pi = find_problem(wstart, np, blockIdx.x);
-    if (done && done[pi]) return;
-    const Prob& p = P[pi];
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
     if (conv_build(MZ, p.lmy, p.f3y) != BUILD) return;  // served by another build
-    const int w = blockIdx.x - wstart[pi];
+    const int w = blockIdx.x - w0;
     const int nsl_img = p.mx + 1, nsl = p.K * nsl_img;
     int s0, G;
     if (p.xcd_remap) {
@@ -1129,9 +1157,11 @@ __global__ __launch_bounds__(conv1_cfg(BUILD, sizeof(T)).nt)
     static_assert(MY == (F3 ? 3 << LMY : 1 << LMY) && (!F3 || A == 12), "split does not match the length");
     extern __shared__ double2 smem_[];
     const int pi = find_problem(wstart, np, blockIdx.x);
-    if (done && done[pi]) return;
-    const Prob& p = P[pi];
-    const int w = blockIdx.x - wstart[pi];
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
+    const int w = blockIdx.x - w0;
     // workgroup w: kx = 8 (j / nwk) + w % 8, image group j % nwk (j = w / 8):
     // the image groups of one kx run back to back on one XCD, whose L2 then
     // holds that kx's kernel spectrum
@@ -1516,10 +1546,12 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     extern __shared__ double2 smem_[];
     __shared__ double red[kNT / 64][kNTerm];
     const int pi = find_problem(wstart, np, blockIdx.x);
-    if (done && done[pi]) return;
-    const Prob& p = P[pi];
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
     if (p.f3x != F3) return;  // served by the other length kind's launch
-    const int t = xcd_item(blockIdx.x - wstart[pi], p.wgi);
+    const int t = xcd_item(blockIdx.x - w0, p.wgi);
     if (t >= p.K * p.tiles) return;
     // z fastest: the tiles that read a plane's rows as z neighbours run
     // back to back on one XCD, while the plane is still in its L2
@@ -1763,9 +1795,11 @@ __global__ __launch_bounds__(kNT) void k_arc(const Prob* __restrict__ P, int np,
                                              const int* __restrict__ done)
 {
     const int pi = find_problem(wstart, np, blockIdx.x);
-    if (done && done[pi]) return;
-    const Prob& p = P[pi];
-    const int w = blockIdx.x - wstart[pi];
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
+    const int w = blockIdx.x - w0;
     const int chunk = w % p.arc_chunks, grp = w / p.arc_chunks;
     // images k0..k1-1 of this workgroup's group, against image k0 - 1
     const int k0 = 1 + grp * p.arc_g, k1 = min(p.K, k0 + p.arc_g);
@@ -2230,10 +2264,12 @@ __global__ __launch_bounds__(kNT) void k_interp(const Prob* __restrict__ P, int 
                                                 const int* __restrict__ skip_if)
 {
     const int pi = find_problem(wstart, np, blockIdx.x);
-    if (done && done[pi]) return;
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
     if (skip_if && skip_if[pi]) return;
-    const Prob& p = P[pi];
-    const int w = blockIdx.x - wstart[pi];
+    const int w = blockIdx.x - w0;
     const int k = w / p.ichunks4, chunk = w - k * p.ichunks4;
     const long long N = p.N, M = 3 * N;
     const T* src = ss + p.s_off;
@@ -2867,9 +2903,11 @@ __global__ __launch_bounds__(kNT) void k_rk_stage(const Prob* __restrict__ P, in
                                                   const int* __restrict__ done)
 {
     const int pi = find_problem(wstart, np, blockIdx.x);
-    if (done && done[pi]) return;
-    const Prob& p = P[pi];
-    const int w = blockIdx.x - wstart[pi];
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
+    const int w = blockIdx.x - w0;
     const int img = w / p.ichunks, chunk = w - img * p.ichunks;
     const long long N = p.N;
     const long long i = (long long)chunk * kNT + threadIdx.x;
@@ -2899,9 +2937,11 @@ __global__ __launch_bounds__(kNT) void k_rk_err(const Prob* __restrict__ P, int 
 {
     __shared__ double red[kNT / 64];
     const int pi = find_problem(wstart, np, blockIdx.x);
-    if (done && done[pi]) return;
-    const Prob& p = P[pi];
-    const int w = blockIdx.x - wstart[pi];
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
+    const int w = blockIdx.x - w0;
     const int img = w / p.ichunks, chunk = w - img * p.ichunks;
     const long long N = p.N;
     const long long i = (long long)chunk * kNT + threadIdx.x;
@@ -2996,9 +3036,11 @@ __global__ __launch_bounds__(kNT) void k_rk_apply(const Prob* __restrict__ P, in
                                                   const int* __restrict__ done)
 {
     const int pi = find_problem(wstart, np, blockIdx.x);
-    if (done && done[pi]) return;
-    const Prob& p = P[pi];
-    const int w = blockIdx.x - wstart[pi];
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
+    const int w = blockIdx.x - w0;
     const int img = w / p.ichunks, chunk = w - img * p.ichunks;
     const long long N = p.N;
     const long long i = (long long)chunk * kNT + threadIdx.x;
@@ -3018,9 +3060,11 @@ __global__ __launch_bounds__(kNT) void k_rk_norm(const Prob* __restrict__ P, int
                                                  T* __restrict__ ss, const int* __restrict__ done, int* flags)
 {
     const int pi = find_problem(wstart, np, blockIdx.x);
-    if (done && done[pi]) return;
-    const Prob& p = P[pi];
-    const int w = blockIdx.x - wstart[pi];
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
+    const int w = blockIdx.x - w0;
     const int img = w / p.ichunks, chunk = w - img * p.ichunks;
     const long long N = p.N;
     const long long i = (long long)chunk * kNT + threadIdx.x;
@@ -3283,9 +3327,11 @@ __global__ __launch_bounds__(kNT) void k_ci_part(const Prob* __restrict__ P, int
     __shared__ double red[kNT / 64][2];
     __shared__ int s_km;
     const int pi = find_problem(wstart, np, blockIdx.x);
-    if (done && done[pi]) return;
-    const Prob& p = P[pi];
-    const int chunk = blockIdx.x - wstart[pi];
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
+    const int chunk = blockIdx.x - w0;
     const int K = p.K, g0 = p.img0;
     if (threadIdx.x < 64) {
         // the first index of the largest energy (NaN energies never count;
