@@ -109,7 +109,7 @@ struct Plan {
     // n_x, n_xp: complex values of the x half-spectra X and of the convolved
     // ones X' kept apart from them (problems not convolved in place)
     long long n_img = 0, n_spin = 0, n_x = 0, n_xp = 0, n_nh = 0, n_ep = 0, n_ap = 0, n_fp = 0, n_fm = 0;
-    size_t lds_xf = 0, lds_xi = 0, lds_conv = 0, lds_conv1[kConvSlots] = {};
+    size_t lds_xf = 0, lds_xi[2] = {}, lds_conv = 0, lds_conv1[kConvSlots] = {};
     size_t scratch_bytes = 0;
     // workspace offsets
     size_t o_P, o_wm, o_tw, o_tw64, o_s, o_ss, o_h, o_nh, o_big, o_ep, o_ap, o_fp, o_E, o_T,
@@ -139,6 +139,21 @@ size_t lds_xinv(const Prob& p, int yt, size_t tsize)
     const int pl = x_padl(p.lmx, p.f3x, (int)tsize);
     const int lines = pl ? padded_len(n, pl) : lds_padded_size(n);
     return (size_t)(2 * p.mx + lines) * 2 * tsize + (size_t)3 * yt * p.nx * tsize;
+}
+
+// whether (and in how much LDS) the two-step inverse x transform serves tiles
+// of yt rows: its three components' lines, with the tile's real field over
+// them afterwards
+bool xinv2_tile(const Prob& p, int yt, size_t tsize, size_t& lds)
+{
+    if (!xinv2_len(p.lmx, p.f3x, (int)tsize)) return false;
+    const Xinv2 c = xinv2_cfg(p.lmx, p.f3x);
+    const int hp = yt / 2;
+    if (3 * hp * c.r1 > xinv2_rounds(c) * kNT) return false;
+    const size_t lines = (size_t)3 * hp * xinv2_line(c, hp, (int)tsize) * 2 * tsize;
+    const size_t field = (size_t)3 * yt * xinv2_hrow(p.nx, hp) * tsize;
+    lds = std::max(lines, field) + (xinv2_twlds(p.mx, p.f3x, (int)tsize) ? 4 * p.mx * tsize : 0);
+    return lds <= kLdsMax / 2;
 }
 
 size_t lds_convg(const Prob& p, int G, size_t tsize)
@@ -237,6 +252,8 @@ void apply_tiles(Prob& p, const Tiles& t, size_t tsize)
     p.nty = (p.ny + p.yt - 1) / p.yt;
     p.tiles = p.nz * p.nty;
     p.wgi = pad8(p.K * p.tiles);
+    size_t lds;
+    p.xi2 = xinv2_tile(p, p.yt, tsize, lds) ? 1 : 0;
     p.gconv = t.gconv;
     p.xcd_remap = (t.gconv == 1) ? 1 : 0;
     if (p.conv1) {
@@ -378,7 +395,9 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         pl.mz = p.mz;
         pl.red_kinds |= p.red1 ? 2 : 1;
         pl.lds_xf = std::max(pl.lds_xf, lds_xfwd(p, p.ytf, pl.tsize));
-        pl.lds_xi = std::max(pl.lds_xi, lds_xinv(p, p.yt, pl.tsize));
+        size_t lxi = lds_xinv(p, p.yt, pl.tsize);
+        if (p.xi2) (void)xinv2_tile(p, p.yt, pl.tsize, lxi);
+        pl.lds_xi[p.f3x] = std::max(pl.lds_xi[p.f3x], lxi);
         size_t& lc = p.conv1 ? pl.lds_conv1[conv_slot(conv_build(p.mz, p.lmy, p.f3y))] : pl.lds_conv;
         lc = std::max(lc, lds_convg(p, p.gconv, pl.tsize));
     }
@@ -517,7 +536,12 @@ struct ssm_ctx {
     struct XMaps { WorkMap m[2]; };
     struct ConvMaps { WorkMap m[kConvSlots]; };
     XMaps wm_xf() const { return {{wm(0, pl.wm_xf[0]), wm(1, pl.wm_xf[1])}}; }
-    XMaps wm_xi() const { return {{wm(2, pl.wm_xi[0]), wm(3, pl.wm_xi[1])}}; }
+    XMaps wm_xi() const
+    {
+        XMaps r = {{wm(2, pl.wm_xi[0]), wm(3, pl.wm_xi[1])}};
+        for (int k = 0; k < 2; ++k) r.m[k].lds = pl.lds_xi[k];
+        return r;
+    }
     ConvMaps wm_conv() const
     {
         ConvMaps r;
@@ -617,7 +641,7 @@ struct Ops {
         if (e != hipSuccess) return e;
         return timed(c, st, KK_XINV, [&] {
             return launch_xinv<T>(c->P(), pl.np, c->wm_xi().m, c->X(), src, s_star, hdst,
-                                  c->at<double>(pl.o_ep), tw, done, mode, tau, fcp, fcd, pl.lds_xi, st);
+                                  c->at<double>(pl.o_ep), tw, done, mode, tau, fcp, fcd, st);
         });
     }
 
@@ -971,7 +995,7 @@ double time_kernel(ssm_ctx* c, int kind, int reps)
                                nullptr, pl.lds_conv, c->stream);
         else
             e = launch_xinv<T>(c->P(), pl.np, c->wm_xi().m, c->X(), s, nullptr, nullptr,
-                               c->at<double>(pl.o_ep), tw, nullptr, EPI_TERMS, 0.0, 0.0, 1.0, pl.lds_xi,
+                               c->at<double>(pl.o_ep), tw, nullptr, EPI_TERMS, 0.0, 0.0, 1.0,
                                c->stream);
         if (e != hipSuccess || hipEventRecord(b, c->stream) != hipSuccess) return 1e30;
         if (hipEventSynchronize(b) != hipSuccess) return 1e30;

@@ -517,9 +517,19 @@ __host__ __device__ __forceinline__ V cmulc_alt(V a, V b)
 {
     return mk<V>(fma(a.y, b.y, a.x * b.x), fma(a.y, b.x, -(a.x * b.y)));
 }
-// radix3_bfly with its twiddle products by cmul_set and cmulc_set
-template <bool INV, typename V>
-__host__ __device__ __forceinline__ void radix3_set(V& a, V& b, V& c, V w1, V w2)
+// A value as a memory round trip leaves it: the compiler can't fuse the
+// operation that made it into the one that takes it.  Where a kernel keeps in
+// registers what another hands over through memory, this keeps the rounding,
+// and so the results, the same.
+template <typename V>
+__device__ __forceinline__ void settle(V& v)
+{
+    asm("" : "+v"(v.x), "+v"(v.y));
+}
+// radix3_bfly with its twiddle products by cmul_set and cmulc_set; ROT: the
+// product with sqrt(3)/2 is rounded by itself
+template <bool INV, bool ROT = false, typename V>
+__device__ __forceinline__ void radix3_set(V& a, V& b, V& c, V w1, V w2)
 {
     using S = decltype(V::x);
     const S h = S(0.5), s3 = S(0.86602540378443864676);  // sqrt(3)/2
@@ -529,7 +539,8 @@ __host__ __device__ __forceinline__ void radix3_set(V& a, V& b, V& c, V w1, V w2
     }
     const V t1 = cadd(b, c), t2 = csub(b, c);
     const V m1 = mk<V>(a.x - h * t1.x, a.y - h * t1.y);
-    const V rot = INV ? mk<V>(-s3 * t2.y, s3 * t2.x) : mk<V>(s3 * t2.y, -s3 * t2.x);
+    V rot = INV ? mk<V>(-s3 * t2.y, s3 * t2.x) : mk<V>(s3 * t2.y, -s3 * t2.x);
+    if constexpr (ROT) settle(rot);
     a = cadd(a, t1);
     b = cadd(m1, rot);
     c = csub(m1, rot);
@@ -537,16 +548,6 @@ __host__ __device__ __forceinline__ void radix3_set(V& a, V& b, V& c, V w1, V w2
         b = cmul_set(b, w1);
         c = cmul_set(c, w2);
     }
-}
-
-// A value as a memory round trip leaves it: the compiler can't fuse the
-// operation that made it into the one that takes it.  Where a kernel keeps in
-// registers what another hands over through memory, this keeps the rounding,
-// and so the results, the same.
-template <typename V>
-__device__ __forceinline__ void settle(V& v)
-{
-    asm("" : "+v"(v.x), "+v"(v.y));
 }
 
 }  // namespace ssm

@@ -133,6 +133,43 @@ __host__ __device__ constexpr int conv_padl(int mz, int lmy, int f3y, int tsize)
            : conv_ct3_shape(mz, lmy, f3y) ? pad_for(tsize == 4 ? SSM_CONV3_PADL_F32 : SSM_CONV3_PADL, lmy)
                                           : 0;
 }
+// The inverse x kernel's transform in two register steps (xinv_two_step), for
+// the lengths whose passes are two: m = 2^lm (32..256; FP64 32..128, whose
+// 256 would spill: 256 x 256 x 8, 48 images 0.90 ms against 0.76) and 3 2^lm
+// (48, 96, 192).  The first pass has radix r1 and nb values at stride nb to a lane;
+// the rest of the transform gives nout outputs to each of r1 lanes.
+struct Xinv2 {
+    int r1, nb, nout;
+};
+__host__ __device__ constexpr bool xinv2_len(int lm, int f3, int tsize)
+{
+    return SSM_X_CT && (f3 ? lm >= 4 && lm <= 6 : lm >= 5 && lm <= (tsize == 4 ? 8 : 7));
+}
+__host__ __device__ constexpr Xinv2 xinv2_cfg(int lm, int f3)
+{
+    const int m = (f3 ? 3 : 1) << lm, r1 = lm == 5 ? 8 : 16;
+    return Xinv2{r1, m / r1, m / r1};
+}
+// its rounds of second-step items per thread (tiles of at most 2048 elements)
+__host__ __device__ constexpr int xinv2_rounds(Xinv2 c) { return (12 + c.nout - 1) / c.nout; }
+// LDS elements from one row pair to the next: nb rows of 2 r1 + 1 values, made
+// an odd multiple of what spreads hp row pairs (consecutive lanes) over the
+// banks
+__host__ __device__ constexpr int xinv2_line(Xinv2 c, int hp, int tsize)
+{
+    const int n = c.nb * (2 * c.r1 + 1), w = tsize == 4 ? 32 : 16, u = hp < w ? w / hp : 1;
+    const int k = (n + u - 1) / u;
+    return u * (k | 1);
+}
+// row stride of the tile's real field, likewise
+__host__ __device__ constexpr int xinv2_hrow(int nx, int hp)
+{
+    const int r = hp < 32 ? 32 / hp : 1;
+    return nx + ((r - nx) & 31);
+}
+// 1: its twiddles have a copy in LDS (0 where that would cost a workgroup)
+__host__ __device__ constexpr int xinv2_twlds(int m, int f3, int tsize) { return f3 || m * tsize <= 512; }
+
 // elements of a buffer of n elements in the pad-padl layout
 __host__ __device__ constexpr int padded_len(int n, int padl) { return padl ? n + (n >> padl) + 1 : n; }
 
@@ -160,6 +197,7 @@ struct Prob {
     int gconv;             // (image, kx) slices per convolution workgroup: consecutive ones (kx fastest),
                            // or images of one kx (monolayers)
     int conv1;             // 1: convolution by k_conv1
+    int xi2;               // 1: inverse x transform by xinv_two_step
     int arc_chunks;        // arc-length workgroups (flat chunks of 3N) per image
     int xcd_remap;         // convolution kernel: group same-kx slices on one XCD
     long long N;           // sites per image
@@ -186,7 +224,7 @@ struct Prob {
 struct WorkMap {
     int* start;      // device: [nprob + 1] prefix sums of workgroup counts
     int total;
-    size_t lds;      // dynamic LDS bytes (monolayer convolution builds)
+    size_t lds;      // dynamic LDS bytes (inverse x, monolayer convolution builds)
 };
 
 // ------------------------------------------------------------------------
@@ -214,7 +252,7 @@ template <typename T>
 // fcp, fcd: coefficients of EPI_FORCE (precession, damping)
 hipError_t launch_xinv(const Prob* P, int np, const WorkMap* wm, const void* Xp, const T* s,
                        T* s_star, T* h, double* epart, const void* tw, const int* done,
-                       int mode, double tau, double fcp, double fcd, size_t lds, hipStream_t st);
+                       int mode, double tau, double fcp, double fcd, hipStream_t st);
 template <typename T>
 hipError_t launch_arc(const Prob* P, int np, const WorkMap& wm, const T* ss, double* apart,
                       const int* done, hipStream_t st);

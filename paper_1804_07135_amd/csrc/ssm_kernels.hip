@@ -1524,13 +1524,176 @@ __device__ __forceinline__ void xinv_load_lines(const char* __restrict__ Xi, cpl
     else rounds(std::false_type{});
 }
 
+// The inverse x transform of a tile's three components in two steps that keep
+// their values in registers, with one LDS exchange between them (hp row pairs
+// of the tile, m = 2^LM or, F3, 3 2^LM; x half-spectra at Xi):
+//   1. a lane reads the r1 values of the first pass from global memory
+//      (frequencies i + nb r of one half of the padded spectrum; those past m
+//      are the conjugates of the mirrored ones) and does that pass;
+//   2. a lane does the rest of the transform of both halves at its nout
+//      positions and joins them; once every lane has read its values, the
+//      real field goes over the lines as hd, rows of stride hrow.
+// Operations and their order are those of xinv_load_lines, fft_lines_x and
+// the steps after them, which serve the other lengths one component at a time
+// with four LDS round trips and, on tiles of 2048 elements, two of the four
+// wavefronts idle in the passes.  k_xinv, us a launch before and after (the
+// rest of it is the epilogue): 64 lattices of 48..96 sites, 16 images, FP32
+// 136 -> 114; 112 x 112, 60 images, FP32 23.4 -> 18.7 and 240 images 59 ->
+// 47; 256 x 256 x 8, 48 images, FP32 441 -> 405; 128 x 128 x 4, 32 images,
+// FP64 68 -> 56; 32 x 32, 10 images, FP64 18.3 -> 12.9.
+template <typename T, int F3, int LM>
+__device__ __forceinline__ void xinv_two_step(const char* __restrict__ Xi, cplx<T>* lines, T* hd,
+                                              const cplx<T>* twl_lds, const cplx<T>* __restrict__ tw, int z, int y0,
+                                              int hp, int lhp, int nx, int nz, int ny, int hrow)
+{
+    using V = cplx<T>;
+    constexpr Xinv2 C = xinv2_cfg(LM, F3);
+    constexpr int R1 = C.r1, NB = C.nb, NO = C.nout, RS = 2 * R1 + 1, m = (F3 ? 3 : 1) << LM;
+    constexpr int TR = xinv2_rounds(C);
+    const V* twl;
+    if constexpr (xinv2_twlds(m, F3, sizeof(T))) twl = twl_lds;
+    else twl = tw + tw_off(LM, F3);
+    const int LS = xinv2_line(C, hp, sizeof(T));
+    const unsigned kstr = (unsigned)(3 * nz * ny) * (unsigned)sizeof(V);
+    const bool odd = ny & 1;
+    // step 1: item (rp, i, half h, component c)
+#pragma unroll 1
+    for (int it = threadIdx.x; it < 6 * NB * hp; it += kNT) {
+        const int rp = it & (hp - 1), q = it >> lhp, ch = q / NB, i = q - ch * NB, h = ch & 1, c = ch >> 1;
+        const int ya = y0 + 2 * rp, k0 = 2 * i + h;
+        // frequency k0 + 2 NB r directly for r < R1 / 2 (and r = R1 / 2 where
+        // that is m itself), else its mirror 2m - k0 - 2 NB r
+        const unsigned row = (unsigned)((c * nz + z) * ny) * (unsigned)sizeof(V);
+        const unsigned od = row + (unsigned)k0 * kstr, om = row - (unsigned)k0 * kstr;
+        auto off = [&](int r) {
+            const bool direct = r < R1 / 2 || (r == R1 / 2 && k0 == 0);
+            return direct ? od + (unsigned)(2 * NB * r) * kstr : om + (unsigned)(2 * m - 2 * NB * r) * kstr;
+        };
+        V v[R1];
+        auto put = [&](int r, V a, V b) {
+            const bool direct = r < R1 / 2 || (r == R1 / 2 && k0 == 0);
+            const V d = mk<V>(a.x - b.y, a.y + b.x), e = mk<V>(a.x + b.y, b.x - a.y);
+            v[r] = mk<V>(direct ? d.x : e.x, direct ? d.y : e.y);
+        };
+        if (!odd) {
+            // (a pair past the lattice reads the last pair: rows transform
+            // independently, and no field of a row past the lattice is used)
+            const unsigned oy = (unsigned)min(ya, ny - 2) * (unsigned)sizeof(V);
+            V a[R1], b[R1];
+#pragma unroll
+            for (int r = 0; r < R1; ++r) load2(reinterpret_cast<const V*>(Xi + (off(r) + oy)), a[r], b[r]);
+#pragma unroll
+            for (int r = 0; r < R1; ++r) put(r, a[r], b[r]);
+        } else {
+            const unsigned oa = (unsigned)min(ya, ny - 1) * (unsigned)sizeof(V);
+            const unsigned ob = (unsigned)min(ya + 1, ny - 1) * (unsigned)sizeof(V);
+            V a[R1], b[R1];
+#pragma unroll
+            for (int r = 0; r < R1; ++r) {
+                a[r] = *reinterpret_cast<const V*>(Xi + (off(r) + oa));
+                b[r] = *reinterpret_cast<const V*>(Xi + (off(r) + ob));
+            }
+#pragma unroll
+            for (int r = 0; r < R1; ++r)
+                put(r, ya < ny ? a[r] : mk<V>(0, 0), ya + 1 < ny ? b[r] : mk<V>(0, 0));
+        }
+        dft_reg<V, R1, true>(v);
+        V* dst = lines + (c * hp + rp) * LS + i * RS + h * R1;
+#pragma unroll
+        for (int r = 0; r < R1; ++r) dst[r] = v[r];
+    }
+    __syncthreads();
+    // step 2: item (rp, position k of the first pass's outputs, component c):
+    // outputs x = k + R1 r, or (F3) k + R1 r + M t
+    const int n2 = 3 * R1 * hp;
+    V out[TR][NO];
+#pragma unroll
+    for (int u = 0; u < TR; ++u) {
+        const int it = threadIdx.x + u * kNT;
+        if (it < n2) {
+            const int rp = it & (hp - 1), q = it >> lhp, k = q & (R1 - 1), c = q / R1;
+            const V* src = lines + (c * hp + rp) * LS + k;
+            V w[2][NO];
+            if constexpr (F3) {
+                constexpr int NR = NO / 3, M = 1 << LM;  // second pass of the sub-lines (NR = 1: none)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) {
+                        V s[NR];
+#pragma unroll
+                        for (int r = 0; r < NR; ++r) {
+                            s[r] = src[(3 * r + t) * RS + h * R1];
+                            if (r) s[r] = cmulc_set(s[r], twl[6 * r * k]);
+                        }
+                        dft_reg<V, NR, true>(s);
+#pragma unroll
+                        for (int r = 0; r < NR; ++r) {
+                            settle(s[r]);
+                            w[h][t * NR + r] = s[r];
+                        }
+                    }
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) {
+                        const int x = k + R1 * r;
+                        radix3_set<true, true>(w[h][r], w[h][NR + r], w[h][2 * NR + r], twl[2 * x], twl[4 * x]);
+                    }
+                }
+#pragma unroll
+                for (int o = 0; o < NO; ++o) {
+                    const int x = k + R1 * (o % NR) + M * (o / NR);
+                    settle(w[0][o]);
+                    settle(w[1][o]);
+                    out[u][o] = cadd(w[0][o], cmulc_set(w[1][o], twl[x]));
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                    for (int r = 0; r < NO; ++r) {
+                        w[h][r] = src[r * RS + h * R1];
+                        if (r) w[h][r] = cmulc_set(w[h][r], twl[2 * r * k]);
+                    }
+                    dft_reg<V, NO, true>(w[h]);
+                }
+#pragma unroll
+                for (int o = 0; o < NO; ++o) {
+                    settle(w[0][o]);
+                    settle(w[1][o]);
+                    out[u][o] = cadd(w[0][o], cmulc_set(w[1][o], twl[k + R1 * o]));
+                }
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < TR; ++u) {
+        const int it = threadIdx.x + u * kNT;
+        if (it < n2) {
+            const int rp = it & (hp - 1), q = it >> lhp, k = q & (R1 - 1), c = q / R1;
+            T* dst = hd + (2 * (c * hp + rp)) * hrow;
+#pragma unroll
+            for (int o = 0; o < NO; ++o) {
+                constexpr int NR = F3 ? NO / 3 : NO, M = 1 << LM;
+                const int x = k + R1 * (o % NR) + (F3 ? M * (o / NR) : 0);
+                if (x < nx) {
+                    dst[x] = out[u][o].x;
+                    dst[hrow + x] = out[u][o].y;
+                }
+            }
+        }
+    }
+    __syncthreads();
+}
+
 // ---------------------------------------------------------------------------
 // k_xinv: x half-spectra of the convolved field -> unit-strength dipolar
 // field of a tile (one component at a time), then the per-site epilogue.
 // Two half-spectra A, B of real rows form Z = A + i B on k = 0..m and
 // conj(A) + i conj(B) on k = m+1..2m-1; the inverse transform gives row a
 // in the real part and row b in the imaginary part.
-// LDS: twiddles (2m) + yt lines of m + the tile's dipolar field (3 yt nx).
+// LDS: twiddles (2m) + yt lines of m + the tile's dipolar field (3 yt nx); with
+// xinv_two_step the lines of all components, and the field over them.
 // ---------------------------------------------------------------------------
 template <typename T, int F3>
 __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? SSM_XINV_WAVES_F32 : 3, 8))) void k_xinv(const Prob* __restrict__ P, int np,
@@ -1566,62 +1729,85 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     const long long N = p.N;
     V* twl = reinterpret_cast<V*>(smem_);
     V* lines = twl + 2 * m;
-    T* hd = reinterpret_cast<T*>(lines + padded_len(yt * m, x_padl(lm, f3, sizeof(T))));
-    load_twiddles(twl, lm, f3, tw);
     // the convolved x half-spectra of the image
     // (as a uniform base and 32-bit byte offsets: an image's spectra span
     // at most 1025 * 3 * 16 * 1024 complex values, under 2^32 bytes)
     const char* const Xi = reinterpret_cast<const char*>(Xp + p.xo_off + (long long)img * (m + 1) * 3 * nz * ny);
-    __syncthreads();
-#pragma unroll 1
-    for (int c = 0; c < 3; ++c) {
-        // kXinvU items per thread per round: their loads are issued
-        // together (no load sits under a branch; an item past the end loads
-        // the values at kx = m and stores nothing), then their LDS writes
-        xinv_load_lines<T, F3>(Xi, lines, c, z, y0, hp, lhp, m, lm, nz, ny, psh);
+    // the tile's dipolar field, rows of stride hrow
+    T* hd;
+    int hrow;
+    if (p.xi2) {
+        const bool tl = xinv2_twlds(m, f3, sizeof(T));
+        if (tl) load_twiddles(twl, lm, f3, tw);
+        else lines = twl;
+        hd = reinterpret_cast<T*>(lines);
+        hrow = xinv2_hrow(nx, hp);
+        auto run = [&](auto lmc) {
+            constexpr int LM = decltype(lmc)::value;
+            xinv_two_step<T, F3, LM>(Xi, lines, hd, twl, tw, z, y0, hp, lhp, nx, nz, ny, hrow);
+        };
+        switch (lm) {
+        case 4: if constexpr (F3) run(std::integral_constant<int, 4>{}); break;
+        case 5: run(std::integral_constant<int, 5>{}); break;
+        case 6: run(std::integral_constant<int, 6>{}); break;
+        case 7: if constexpr (!F3) run(std::integral_constant<int, 7>{}); break;
+        default: if constexpr (!F3 && sizeof(T) == 4) run(std::integral_constant<int, 8>{}); break;
+        }
+    } else {
+        hd = reinterpret_cast<T*>(lines + padded_len(yt * m, x_padl(lm, f3, sizeof(T))));
+        hrow = nx;
+        load_twiddles(twl, lm, f3, tw);
         __syncthreads();
-        fft_lines_x<V, true>(lines, yt, lm, f3, twl);
-        __syncthreads();
-        if constexpr (F3) {
-            // the inverse radix-3 step (decimation in time) on the way out:
-            // sub-line positions k of both half lines give x = k + t 2^lm
-            const int M = 1 << lm;
-            for (int idx = threadIdx.x; idx < (hp << lm); idx += kNT) {
-                const int rp = idx >> lm, k = idx & (M - 1);
-                if (k >= nx) continue;
-                const int ie = (2 * rp) * m + k, io = ie + m;
-                V e[3], o[3];
-#pragma unroll
-                for (int t = 0; t < 3; ++t) {
-                    const int a = ie + t * M, b = io + t * M;
-                    e[t] = lines[a + (a >> psh)];
-                    o[t] = lines[b + (b >> psh)];
-                }
-                const V w1 = twl[2 * k], w2 = twl[4 * k];
-                radix3_bfly<true>(e[0], e[1], e[2], w1, w2);
-                radix3_bfly<true>(o[0], o[1], o[2], w1, w2);
-#pragma unroll
-                for (int t = 0; t < 3; ++t) {
-                    const int x = k + t * M;
-                    if (x < nx) {
-                        const V ot = cmulc(o[t], twl[x]);
-                        hd[(c * yt + 2 * rp) * nx + x] = e[t].x + ot.x;
-                        hd[(c * yt + 2 * rp + 1) * nx + x] = e[t].y + ot.y;
+    #pragma unroll 1
+        for (int c = 0; c < 3; ++c) {
+            // kXinvU items per thread per round: their loads are issued
+            // together (no load sits under a branch; an item past the end loads
+            // the values at kx = m and stores nothing), then their LDS writes
+            xinv_load_lines<T, F3>(Xi, lines, c, z, y0, hp, lhp, m, lm, nz, ny, psh);
+            __syncthreads();
+            fft_lines_x<V, true>(lines, yt, lm, f3, twl);
+            __syncthreads();
+            if constexpr (F3) {
+                // the inverse radix-3 step (decimation in time) on the way out:
+                // sub-line positions k of both half lines give x = k + t 2^lm
+                const int M = 1 << lm;
+                for (int idx = threadIdx.x; idx < (hp << lm); idx += kNT) {
+                    const int rp = idx >> lm, k = idx & (M - 1);
+                    if (k >= nx) continue;
+                    const int ie = (2 * rp) * m + k, io = ie + m;
+                    V e[3], o[3];
+    #pragma unroll
+                    for (int t = 0; t < 3; ++t) {
+                        const int a = ie + t * M, b = io + t * M;
+                        e[t] = lines[a + (a >> psh)];
+                        o[t] = lines[b + (b >> psh)];
+                    }
+                    const V w1 = twl[2 * k], w2 = twl[4 * k];
+                    radix3_bfly<true>(e[0], e[1], e[2], w1, w2);
+                    radix3_bfly<true>(o[0], o[1], o[2], w1, w2);
+    #pragma unroll
+                    for (int t = 0; t < 3; ++t) {
+                        const int x = k + t * M;
+                        if (x < nx) {
+                            const V ot = cmulc(o[t], twl[x]);
+                            hd[(c * yt + 2 * rp) * nx + x] = e[t].x + ot.x;
+                            hd[(c * yt + 2 * rp + 1) * nx + x] = e[t].y + ot.y;
+                        }
                     }
                 }
+            } else {
+                for (int idx = threadIdx.x; idx < hp * m; idx += kNT) {
+                    const int rp = idx >> lm, x = idx & (m - 1);
+                    if (x >= nx) continue;
+                    const int ie = (2 * rp) * m + x, io = ie + m;
+                    const V e = lines[ie + (ie >> psh)];
+                    const V o = cmulc(lines[io + (io >> psh)], twl[x]);
+                    hd[(c * yt + 2 * rp) * nx + x] = e.x + o.x;
+                    hd[(c * yt + 2 * rp + 1) * nx + x] = e.y + o.y;
+                }
             }
-        } else {
-            for (int idx = threadIdx.x; idx < hp * m; idx += kNT) {
-                const int rp = idx >> lm, x = idx & (m - 1);
-                if (x >= nx) continue;
-                const int ie = (2 * rp) * m + x, io = ie + m;
-                const V e = lines[ie + (ie >> psh)];
-                const V o = cmulc(lines[io + (io >> psh)], twl[x]);
-                hd[(c * yt + 2 * rp) * nx + x] = e.x + o.x;
-                hd[(c * yt + 2 * rp + 1) * nx + x] = e.y + o.y;
-            }
+            __syncthreads();
         }
-        __syncthreads();
     }
 
     // Per-site epilogue.  Each thread owns one column x and walks a run of
@@ -1720,8 +1906,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
                 const double dmx = -(xp[2] - xm[2]);
                 const double dmy = -((double)cp[2] - (double)cm[2]);
                 const double dmz = -(-xp[0] + xm[0] - (double)cp[1] + (double)cm[1]);
-                const double hu[3] = {(double)hd[(0 * yt + r) * nx + x], (double)hd[(1 * yt + r) * nx + x],
-                                      (double)hd[(2 * yt + r) * nx + x]};
+                const double hu[3] = {(double)hd[(0 * yt + r) * hrow + x], (double)hd[(1 * yt + r) * hrow + x],
+                                      (double)hd[(2 * yt + r) * hrow + x]};
                 double h[3];
                 h[0] = J * nb[0] + dm * dmx + D * hu[0];
                 h[1] = J * nb[1] + dm * dmy + D * hu[1];
@@ -2746,13 +2932,13 @@ hipError_t launch_conv(int mz, const Prob* P, int np, const WorkMap* wm, void* X
 template <typename T>
 hipError_t launch_xinv(const Prob* P, int np, const WorkMap* wm, const void* Xp, const T* s,
                        T* s_star, T* h, double* epart, const void* tw, const int* done, int mode,
-                       double tau, double fcp, double fcd, size_t lds, hipStream_t st)
+                       double tau, double fcp, double fcd, hipStream_t st)
 {
     if (wm[0].total)
-        hipLaunchKernelGGL((k_xinv<T, 0>), dim3(wm[0].total), dim3(kNT), lds, st, P, np, wm[0].start,
+        hipLaunchKernelGGL((k_xinv<T, 0>), dim3(wm[0].total), dim3(kNT), wm[0].lds, st, P, np, wm[0].start,
                            (const cplx<T>*)Xp, s, s_star, h, epart, (const cplx<T>*)tw, done, mode, tau, fcp, fcd);
     if (wm[1].total)
-        hipLaunchKernelGGL((k_xinv<T, 1>), dim3(wm[1].total), dim3(kNT), lds, st, P, np, wm[1].start,
+        hipLaunchKernelGGL((k_xinv<T, 1>), dim3(wm[1].total), dim3(kNT), wm[1].lds, st, P, np, wm[1].start,
                            (const cplx<T>*)Xp, s, s_star, h, epart, (const cplx<T>*)tw, done, mode, tau, fcp, fcd);
     return hipGetLastError();
 }
@@ -3564,7 +3750,7 @@ hipError_t launch_fill_double(double* p, int n, double v, hipStream_t st)
     template hipError_t launch_xinv<T>(const Prob*, int, const WorkMap*, const void*,              \
                                        const T*,                                                    \
                                        T*, T*, double*, const void*, const int*, int, double,     \
-                                       double, double, size_t, hipStream_t);                       \
+                                       double, double, hipStream_t);                               \
     template hipError_t launch_arc<T>(const Prob*, int, const WorkMap&, const T*, double*,        \
                                       const int*, hipStream_t);                                    \
     template hipError_t launch_interp<T>(const Prob*, int, const WorkMap&, const T*, T*,          \
