@@ -123,6 +123,11 @@ struct Plan {
     size_t o_s2 = 0, o_kci = 0, o_splok = 0, o_cic = 0;
 };
 
+// Default tile shapes; autotuning may replace them.  Workgroups should fit
+// three to a CU (LDS <= 52 KiB) and write or read >= 64-byte runs of the
+// [img][kx][c][z][y] spectra.
+constexpr size_t kLdsTarget = 52 * 1024;
+
 // LDS bytes of the FFT kernels: twiddle table (2m complex) + line buffer in
 // the padded layout of ssm_fft.hpp (+ the tile's real field for k_xinv).
 size_t lds_xfwd(const Prob& p, int yt, size_t tsize)
@@ -156,12 +161,24 @@ bool xinv2_tile(const Prob& p, int yt, size_t tsize, size_t& lds)
     return lds <= kLdsMax / 2;
 }
 
+// most slices of a workgroup of k_convz: as many as leave three workgroups to
+// a CU (at least one)
+int convz_gmax(const Prob& p, size_t tsize)
+{
+    const int build = conv_build(p.mz, p.lmy, p.f3y);
+    int g = 1;
+    while (g < 16 && convz_lds(build, g + 1, p.nz, (int)tsize) <= kLdsTarget) ++g;
+    return g;
+}
+
 size_t lds_convg(const Prob& p, int G, size_t tsize)
 {
-    if (p.conv1) {
-        const Conv1Cfg c = conv1_cfg(conv_build(p.mz, p.lmy, p.f3y), (int)tsize);
+    const int build = conv_build(p.mz, p.lmy, p.f3y);
+    if (p.conv1 == 1) {
+        const Conv1Cfg c = conv1_cfg(build, (int)tsize);
         return conv1_lds(c, std::min(G, c.g), (int)tsize);
     }
+    if (p.conv1 == 2) return convz_lds(build, std::min(G, convz_gmax(p, tsize)), p.nz, (int)tsize);
     const int n = G * 3 * p.nz * p.my;
     if (conv_ct_shape(p.mz, p.lmy, p.f3y) || conv_ct3_shape(p.mz, p.lmy, p.f3y))
         return (size_t)(2 * p.my + padded_len(n, conv_padl(p.mz, p.lmy, p.f3y, (int)tsize))) * 2 * tsize;
@@ -202,11 +219,6 @@ ssm_status check_problems(const ssm_problem* pr, int np, int prec, std::string& 
     return SSM_OK;
 }
 
-// Default tile shapes; autotuning may replace them.  Workgroups should fit
-// three to a CU (LDS <= 52 KiB) and write or read >= 64-byte runs of the
-// [img][kx][c][z][y] spectra.
-constexpr size_t kLdsTarget = 52 * 1024;
-
 // batch_rows: image rows (K nz ny), batch_slices: convolution slices
 // (K (m_x + 1)) of every problem of the context, for the occupancy of a
 // launch covering them all
@@ -230,7 +242,8 @@ Tiles default_tiles(const Prob& p, size_t tsize, long long batch_rows, long long
     t.yt = yi;
     const int per = 3 * p.nz * p.ny;
     int gmax = std::max(1, kConvElems / per);
-    if (p.conv1) gmax = conv1_cfg(conv_build(p.mz, p.lmy, p.f3y), (int)tsize).g;
+    if (p.conv1 == 1) gmax = conv1_cfg(conv_build(p.mz, p.lmy, p.f3y), (int)tsize).g;
+    if (p.conv1 == 2) gmax = convz_gmax(p, tsize);
     while (!p.conv1 && gmax > 1 && lds_convg(p, gmax, tsize) > kLdsTarget) --gmax;
     // as many slices per workgroup as keep about 1024 workgroups in a
     // launch over the whole batch (small lattices: several wavefronts' line
@@ -259,7 +272,8 @@ void apply_tiles(Prob& p, const Tiles& t, size_t tsize)
     if (p.conv1) {
         // at most what the build's LDS holds, and the images of a kx spread
         // evenly over its workgroups
-        const int g = std::min(t.gconv, conv1_cfg(conv_build(p.mz, p.lmy, p.f3y), (int)tsize).g);
+        const int g = std::min(t.gconv, p.conv1 == 2 ? convz_gmax(p, tsize)
+                                                     : conv1_cfg(conv_build(p.mz, p.lmy, p.f3y), (int)tsize).g);
         const int n = (p.K + g - 1) / g;
         p.gconv = (p.K + n - 1) / n;
     }
@@ -317,7 +331,7 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         p.pz = q.nz > 1 ? 2 * p.mz : 1;
         p.nhz = q.nz > 1 ? 2 : 1;
         p.N = (long long)q.nx * q.ny * q.nz;
-        p.conv1 = conv1_shape(p.mz, p.lmy, p.f3y) ? 1 : 0;
+        p.conv1 = conv_inplace(p.nz, p.mz, conv_build(p.mz, p.lmy, p.f3y), (int)pl.tsize);
         // one component per forward x workgroup until a launch has 4096
         // tiles (of about 4096 elements) without it: shorter chains and more
         // workgroups (64 x 64, 20 images, FP32: 11.0 -> 7.8 us; 64 lattices
@@ -398,7 +412,7 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         size_t lxi = lds_xinv(p, p.yt, pl.tsize);
         if (p.xi2) (void)xinv2_tile(p, p.yt, pl.tsize, lxi);
         pl.lds_xi[p.f3x] = std::max(pl.lds_xi[p.f3x], lxi);
-        size_t& lc = p.conv1 ? pl.lds_conv1[conv_slot(conv_build(p.mz, p.lmy, p.f3y))] : pl.lds_conv;
+        size_t& lc = p.conv1 ? pl.lds_conv1[conv_slot(conv_build(p.mz, p.lmy, p.f3y), 1)] : pl.lds_conv;
         lc = std::max(lc, lds_convg(p, p.gconv, pl.tsize));
     }
     for (Prob& q : pl.P)
@@ -430,7 +444,7 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
     }
     for (int j = 0; j < kConvSlots; ++j)
         prefix(pl.wm_conv[j], [j](const Prob& p) {
-            return conv_slot(conv_build(p.mz, p.lmy, p.f3y)) == j ? (int)conv_wgs(p) : 0;
+            return conv_slot(conv_build(p.mz, p.lmy, p.f3y), p.conv1) == j ? (int)conv_wgs(p) : 0;
         });
     prefix(pl.wm_arc, [](const Prob& p) { return p.arc_chunks * p.arc_ng; });
     prefix(pl.wm_site, [](const Prob& p) { return p.K * p.ichunks; });

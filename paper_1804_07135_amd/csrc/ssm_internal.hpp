@@ -52,11 +52,6 @@ __host__ __device__ constexpr bool conv_ct3_shape(int mz, int lmy, int f3y)
 {
     return SSM_CONV_CT && f3y && mz <= 8 && lmy >= 4 && lmy <= 6;
 }
-// monolayers (nz = 1): one kernel (k_conv1) at the same y lengths
-__host__ __device__ constexpr bool conv1_shape(int mz, int lmy, int f3y)
-{
-    return mz == 1 && (conv_ct_shape(mz, lmy, f3y) || conv_ct3_shape(mz, lmy, f3y));
-}
 // build serving a problem: the y length's log2 (5..8) for the compile-time
 // power-of-two builds, 16 + log2 of the power-of-two factor (20..22) for the
 // compile-time 3 2^a builds, 0 for the runtime-length one
@@ -90,6 +85,29 @@ __host__ __device__ constexpr int conv1_line(Conv1Cfg c) { return c.B * (2 * c.A
 __host__ __device__ constexpr size_t conv1_lds(Conv1Cfg c, int G, int tsize)
 {
     return (size_t)((c.twlds ? 2 * c.A * c.B : 0) + G * 3 * conv1_line(c)) * 2 * tsize;
+}
+// the same split for several layers (k_convz): G slices of 3 nz lines
+__host__ __device__ constexpr int convz_twlds(int build, int tsize) { return build >= 16 || (build <= 8 ? (1 << build) : 0) * tsize <= 512; }
+__host__ __device__ constexpr size_t convz_lds(int build, int G, int nz, int tsize)
+{
+    const Conv1Cfg c = conv1_cfg(build, tsize);
+    return (size_t)((convz_twlds(build, tsize) ? 2 * c.A * c.B : 0) + G * 3 * nz * conv1_line(c)) * 2 * tsize;
+}
+
+// Whether the in-place kernels take a problem: monolayers always; several
+// layers where one slice's lines of both halves fit kConvzLds: two workgroups
+// to a CU, where it was measured the faster; one to a CU would hold fewer
+// wavefronts than k_conv's three (256 x 256 x 8) or, in FP64, not fit.  (_all,
+// _min: every layer count, the smallest one, of a padded count mz.)
+constexpr size_t kConvzLds = 80 * 1024;
+__host__ __device__ constexpr int conv_inplace(int nz, int mz, int build, int tsize)
+{
+    return build == 0 || mz > 8 ? 0 : mz == 1 ? 1 : convz_lds(build, 1, nz, tsize) <= kConvzLds ? 2 : 0;
+}
+__host__ __device__ constexpr bool conv_inplace_all(int mz, int build, int tsize) { return conv_inplace(mz, mz, build, tsize) != 0; }
+__host__ __device__ constexpr bool conv_inplace_min(int mz, int build, int tsize)
+{
+    return conv_inplace(mz / 2 + 1, mz, build, tsize) != 0;
 }
 
 // LDS layout of the line buffers (pad_for, padx in ssm_fft.hpp).  The
@@ -196,7 +214,7 @@ struct Prob {
     int img0;              // index of this problem's first image in batch-wide arrays
     int gconv;             // (image, kx) slices per convolution workgroup: consecutive ones (kx fastest),
                            // or images of one kx (monolayers)
-    int conv1;             // 1: convolution by k_conv1
+    int conv1;             // convolution in place, both halves together: 1 by k_conv1, 2 by k_convz
     int xi2;               // 1: inverse x transform by xinv_two_step
     int arc_chunks;        // arc-length workgroups (flat chunks of 3N) per image
     int xcd_remap;         // convolution kernel: group same-kx slices on one XCD
@@ -235,8 +253,12 @@ struct WorkMap {
 // of its own, in which the problems of other kinds have no workgroups; a
 // kind whose map is empty is not launched.  wm[0..1]: x length kinds
 // (f3x); wm[conv_slot(b)]: convolution build b.
-constexpr int kConvSlots = 8;
-__host__ __device__ constexpr int conv_slot(int b) { return b == 0 ? 0 : (b <= 8 ? b - 4 : b - 15); }
+// (the in-place kernels have slots of their own, kConvSlots / 2 further on)
+constexpr int kConvSlots = 16;
+__host__ __device__ constexpr int conv_slot(int b, int inplace)
+{
+    return (inplace ? kConvSlots / 2 : 0) + (b == 0 ? 0 : (b <= 8 ? b - 4 : b - 15));
+}
 template <typename T>
 hipError_t launch_xfwd(const Prob* P, int np, const WorkMap* wm, const T* s, void* X,
                        const void* tw, const int* done, size_t lds, hipStream_t st);

@@ -535,19 +535,108 @@ __device__ __forceinline__ void conv_fft_y(V* lines, int nlines, int lmy, int f3
     else fft_lines<V, INV, SSM_CONV_RADIX_BITS>(lines, nlines, 1 << lmy, lmy, twl);
 }
 
-// z-phase of the compile-time-length convolution bodies: for every column
-// (slice g, position py, y frequency qy) of the G slices in LDS, both z
-// halves of the padded z transform (length-MZ DFTs), the 3x3 kernel-
-// spectrum multiply, the inverse and the sum of the halves.  NZ > 0 fixes
-// nz at compile time.  y length MY = 2^LMY, or 3 2^LMY (F3) with the
-// permuted frequency order of the 3 2^a transforms.
-template <typename T, int MZ, int LMY, int NZ, int PADL, int F3 = 0>
-__device__ __forceinline__ void conv_zphase(const Prob& p, int G, int kx0, int hy, cplx<T>* lines,
-                                            const T* __restrict__ nhat, const cplx<T>* __restrict__ tw)
+// The z-phase of one column: at x frequency kx and y frequency 2 qy + hy, the
+// values of layer zz and component c lie at cell[(c nz + zz) ls].  Both z
+// halves of the padded z transform (length-MZ DFTs), the 3x3 kernel-spectrum
+// multiply, the inverse and the sum of the halves, in place.  MY = 2^LMY, or 3
+// 2^LMY (F3).  MIR: mirrored rows of the kernel spectrum are read once; WAIT:
+// the second z half's loads wait for the first half's last result (hoisted
+// above it they would spill).
+template <typename T, int MZ, int LMY, int F3, bool MIR, bool WAIT>
+__device__ __forceinline__ void conv_zcolumn(const Prob& p, int kx, int hy, int qy, cplx<T>* cell, int ls,
+                                             const T* __restrict__ nhat, const cplx<T>* __restrict__ tw)
 {
     using V = cplx<T>;
     constexpr int MY = (F3 ? 3 : 1) << LMY;
-    const int nz = NZ > 0 ? NZ : p.nz, nhz = p.nhz, nsl_img = p.mx + 1;
+    const int nz = p.nz, nhz = p.nhz;
+    V b[3][MZ];
+    // the two z halves as separate bodies (hz a compile-time constant:
+    // the even half has no twiddles, and no selects between the halves)
+    auto zhalf = [&](auto hzc) {
+        constexpr int hz = decltype(hzc)::value;
+        const T* nh = nhat + p.nh_off + (((((long long)kx * nhz + hz) * 2 + hy) * MZ) * 6 * MY) + qy;
+        if constexpr (WAIT && hz == 1) asm volatile("" : "+v"(nh), "+v"(b[2][MZ - 1].x));
+        // the column's kernel-spectrum rows, loaded before its LDS reads
+        // and z transforms so that their latency overlaps that work.
+        // z frequency kz = 2r + hz and its mirror -kz (mod 2 MZ) hold
+        // the same spectrum up to the sign of the z-odd components xz
+        // and yz (the tensor is even in z except for those), so each
+        // column reads only the rows r <= mirror (9 of 16 for MZ = 8)
+        // and the unrolled loop folds the repeated loads (not for 8
+        // layers with y lengths below 256, where keeping the shared rows
+        // live costs more registers than it saves)
+        constexpr bool kMir = SSM_CONV_NH_MIRROR && MIR;
+        T nv[MZ][6];
+#pragma unroll
+        for (int r = 0; r < MZ; ++r) {
+            const bool mir = kMir && (hz == 0 ? 2 * r > MZ : 2 * r >= MZ);
+            const int rs = mir ? (hz == 0 ? MZ - r : MZ - 1 - r) : r;
+            const T* q6 = nh + rs * 6 * MY;
+            nv[r][0] = q6[0];
+            nv[r][1] = q6[MY];
+            nv[r][2] = mir ? -q6[2 * MY] : q6[2 * MY];
+            nv[r][3] = q6[3 * MY];
+            nv[r][4] = mir ? -q6[4 * MY] : q6[4 * MY];
+            nv[r][5] = q6[5 * MY];
+            // (the sign kept out of the products below, so that they are
+            // summed as with rows of their own)
+            if constexpr (WAIT && sizeof(T) == 4)
+                if (mir) asm("" : "+v"(nv[r][2]), "+v"(nv[r][4]));
+        }
+        V a[3][MZ];
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int zz = 0; zz < MZ; ++zz) {
+                V v = (zz < nz) ? cell[(c * nz + zz) * ls] : mk<V>(0, 0);
+                if constexpr (hz == 1) v = twz<false, V, MZ>(v, zz, tw);
+                a[c][zz] = v;
+            }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) dft_reg<V, MZ, false>(a[c]);
+#pragma unroll
+        for (int r = 0; r < MZ; ++r) {
+            const T nxx = nv[r][0], nxy = nv[r][1], nxz = nv[r][2];
+            const T nyy = nv[r][3], nyz = nv[r][4], nzz = nv[r][5];
+            const V sx = a[0][r], sy = a[1][r], sz = a[2][r];
+            a[0][r] = mk<V>(nxx * sx.x + nxy * sy.x + nxz * sz.x, nxx * sx.y + nxy * sy.y + nxz * sz.y);
+            a[1][r] = mk<V>(nxy * sx.x + nyy * sy.x + nyz * sz.x, nxy * sx.y + nyy * sy.y + nyz * sz.y);
+            a[2][r] = mk<V>(nxz * sx.x + nyz * sy.x + nzz * sz.x, nxz * sx.y + nyz * sy.y + nzz * sz.y);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) dft_reg<V, MZ, true>(a[c]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int zz = 0; zz < MZ; ++zz) {
+                V v = a[c][zz];
+                if constexpr (hz == 1) {
+                    v = twz<true, V, MZ>(v, zz, tw);
+                    b[c][zz] = cadd(b[c][zz], v);
+                } else {
+                    b[c][zz] = v;
+                }
+            }
+    };
+    zhalf(std::integral_constant<int, 0>{});
+    if (nhz > 1) zhalf(std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int zz = 0; zz < MZ; ++zz)
+            if (zz < nz) cell[(c * nz + zz) * ls] = b[c][zz];
+}
+
+// z-phase of the compile-time-length convolution bodies: every column (slice
+// g, position py, y frequency qy) of the G slices in LDS.  y length MY =
+// 2^LMY, or 3 2^LMY (F3) with the permuted frequency order of the 3 2^a
+// transforms.
+template <typename T, int MZ, int LMY, int PADL, int F3 = 0>
+__device__ __forceinline__ void conv_zphase(const Prob& p, int G, int kx0, int hy, cplx<T>* lines,
+                                            const T* __restrict__ nhat, const cplx<T>* __restrict__ tw)
+{
+    constexpr int MY = (F3 ? 3 : 1) << LMY;
+    const int nz = p.nz, nsl_img = p.mx + 1;
     int col0 = threadIdx.x;
     asm volatile("" : "+v"(col0));
     for (int col = col0; col < G * MY; col += kNT) {
@@ -555,80 +644,10 @@ __device__ __forceinline__ void conv_zphase(const Prob& p, int G, int kx0, int h
         const int qy = F3 ? unperm3(py, LMY) : py;
         int kx = kx0 + g;
         while (kx >= nsl_img) kx -= nsl_img;
-        // padded offsets: cbase % 2^PADL = py % 2^PADL and the line offsets
-        // are multiples of the line length, so padx distributes
-        const int cbase = padx<PADL>(g * 3 * nz * MY + py);
-        V b[3][MZ];
-        // the two z halves as separate bodies (hz a compile-time constant:
-        // the even half has no twiddles, and no selects between the halves)
-        auto zhalf = [&](auto hzc) {
-            constexpr int hz = decltype(hzc)::value;
-            const T* nh = nhat + p.nh_off + (((((long long)kx * nhz + hz) * 2 + hy) * MZ) * 6 * MY) + qy;
-            // the column's kernel-spectrum rows, loaded before its LDS reads
-            // and z transforms so that their latency overlaps that work.
-            // z frequency kz = 2r + hz and its mirror -kz (mod 2 MZ) hold
-            // the same spectrum up to the sign of the z-odd components xz
-            // and yz (the tensor is even in z except for those), so each
-            // column reads only the rows r <= mirror (9 of 16 for MZ = 8)
-            // and the unrolled loop folds the repeated loads (not for 8
-            // layers with y lengths below 256, where keeping the shared rows
-            // live costs more registers than it saves)
-            constexpr bool kMir = SSM_CONV_NH_MIRROR && (MZ <= 4 || LMY >= 8);
-            T nv[MZ][6];
-#pragma unroll
-            for (int r = 0; r < MZ; ++r) {
-                const bool mir = kMir && (hz == 0 ? 2 * r > MZ : 2 * r >= MZ);
-                const int rs = mir ? (hz == 0 ? MZ - r : MZ - 1 - r) : r;
-                const T* q6 = nh + rs * 6 * MY;
-                nv[r][0] = q6[0];
-                nv[r][1] = q6[MY];
-                nv[r][2] = mir ? -q6[2 * MY] : q6[2 * MY];
-                nv[r][3] = q6[3 * MY];
-                nv[r][4] = mir ? -q6[4 * MY] : q6[4 * MY];
-                nv[r][5] = q6[5 * MY];
-            }
-            V a[3][MZ];
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-#pragma unroll
-                for (int zz = 0; zz < MZ; ++zz) {
-                    V v = (zz < nz) ? lines[cbase + padx<PADL>((c * nz + zz) * MY)] : mk<V>(0, 0);
-                    if constexpr (hz == 1) v = twz<false, V, MZ>(v, zz, tw);
-                    a[c][zz] = v;
-                }
-#pragma unroll
-            for (int c = 0; c < 3; ++c) dft_reg<V, MZ, false>(a[c]);
-#pragma unroll
-            for (int r = 0; r < MZ; ++r) {
-                const T nxx = nv[r][0], nxy = nv[r][1], nxz = nv[r][2];
-                const T nyy = nv[r][3], nyz = nv[r][4], nzz = nv[r][5];
-                const V sx = a[0][r], sy = a[1][r], sz = a[2][r];
-                a[0][r] = mk<V>(nxx * sx.x + nxy * sy.x + nxz * sz.x, nxx * sx.y + nxy * sy.y + nxz * sz.y);
-                a[1][r] = mk<V>(nxy * sx.x + nyy * sy.x + nyz * sz.x, nxy * sx.y + nyy * sy.y + nyz * sz.y);
-                a[2][r] = mk<V>(nxz * sx.x + nyz * sy.x + nzz * sz.x, nxz * sx.y + nyz * sy.y + nzz * sz.y);
-            }
-#pragma unroll
-            for (int c = 0; c < 3; ++c) dft_reg<V, MZ, true>(a[c]);
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-#pragma unroll
-                for (int zz = 0; zz < MZ; ++zz) {
-                    V v = a[c][zz];
-                    if constexpr (hz == 1) {
-                        v = twz<true, V, MZ>(v, zz, tw);
-                        b[c][zz] = cadd(b[c][zz], v);
-                    } else {
-                        b[c][zz] = v;
-                    }
-                }
-        };
-        zhalf(std::integral_constant<int, 0>{});
-        if (nhz > 1) zhalf(std::integral_constant<int, 1>{});
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-#pragma unroll
-            for (int zz = 0; zz < MZ; ++zz)
-                if (zz < nz) lines[cbase + padx<PADL>((c * nz + zz) * MY)] = b[c][zz];
+        // padded offsets: the column's first % 2^PADL = py % 2^PADL and the
+        // line offsets are multiples of the line length, so padx distributes
+        conv_zcolumn<T, MZ, LMY, F3, (MZ <= 4 || LMY >= 8), false>(p, kx, hy, qy, lines + padx<PADL>(g * 3 * nz * MY + py), padx<PADL>(MY), nhat,
+                                     tw);
     }
 }
 
@@ -719,7 +738,7 @@ __device__ __forceinline__ void conv_body_ct(const Prob& p, int s0, int G, cplx<
         // z-phase: per column (slice, qy), z DFT halves, 3x3 multiply,
         // inverse (nz at run time: compile-time offsets make the scheduler
         // hoist every load of the column and run out of registers)
-        conv_zphase<T, MZ, LMY, 0, PADL>(p, G, kx0, hy, lines, nhat, tw);
+        conv_zphase<T, MZ, LMY, PADL>(p, G, kx0, hy, lines, nhat, tw);
         __syncthreads();
 
         // inverse y transform; the last pass writes y half hy = 0 to the
@@ -1008,7 +1027,7 @@ __device__ __forceinline__ void conv_body_ct3(const Prob& p, int s0, int G, cplx
         }
         __syncthreads();
 
-        conv_zphase<T, MZ, LMY, 0, PADL, 1>(p, G, kx0, hy, lines, nhat, tw);
+        conv_zphase<T, MZ, LMY, PADL, 1>(p, G, kx0, hy, lines, nhat, tw);
         __syncthreads();
 
         lane = threadIdx.x;
@@ -1085,7 +1104,6 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     bool off;
     const Prob& p = problem(P, pi, wstart, done, w0, off);
     if (off) return;
-    if (conv_build(MZ, p.lmy, p.f3y) != BUILD) return;  // served by another build
     const int w = blockIdx.x - w0;
     const int nsl_img = p.mx + 1, nsl = p.K * nsl_img;
     int s0, G;
@@ -1111,6 +1129,112 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     if constexpr (BUILD >= 16) conv_body_ct3<T, MZ, BUILD - 16>(p, s0, G, X, nhat, tw, sm);
     else if constexpr (BUILD > 0) conv_body_ct<T, MZ, BUILD>(p, s0, G, X, nhat, tw, sm);
     else conv_body<T, MZ>(p, s0, G, X, nhat, tw, sm);
+}
+
+// First pass of both halves of a line's padded y transform, for the inputs e
+// at stride B from j (those beyond ny count as zero; A of them, F3: y = j + B
+// (r + 4 t)): half 0 from e, half 1 from e twiddled by W_{2m}^y, their outputs
+// to dst[0..A) and dst[A..2A) (F3: output k of sub-line t at 3 k + t).
+template <typename V, int A, int B, int F3>
+__device__ __forceinline__ void conv_first_pass(V (&e)[A], V (&o)[A], int j, int ny, const V* twl, V* dst)
+{
+    if constexpr (F3) {
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+            o[a] = cmul_set(e[a], twl[j + B * a]);
+            if (j + B * a >= ny) e[a] = o[a] = mk<V>(0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const V w1 = twl[2 * (j + B * r)], w2 = twl[4 * (j + B * r)];
+            radix3_set<false>(e[r], e[r + 4], e[r + 8], w1, w2);
+            radix3_set<false>(o[r], o[r + 4], o[r + 8], w1, w2);
+        }
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            V u[4], v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { u[r] = e[4 * t + r]; v[r] = o[4 * t + r]; }
+            dft_reg<V, 4, false>(u);
+            dft_reg<V, 4, false>(v);
+            // sub-line t, output k: column 3 k + t
+#pragma unroll
+            for (int k = 0; k < 4; ++k) { dst[3 * k + t] = u[k]; dst[A + 3 * k + t] = v[k]; }
+        }
+    } else {
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+            if (j + B * a >= ny) e[a] = mk<V>(0, 0);
+            o[a] = cmul_set(e[a], twl[j + B * a]);
+        }
+        dft_reg<V, A, false>(e);
+        dft_reg<V, A, false>(o);
+#pragma unroll
+        for (int a = 0; a < A; ++a) { dst[a] = e[a]; dst[A + a] = o[a]; }
+    }
+}
+
+// Last inverse pass of both halves of a line whose first inverse pass left its
+// rows at row0, half 1 un-twiddled and added to half 0, onto the line at dst.
+// F3: y = j + B (r + 4 t) from row j; else y = j + A r from column j.
+template <typename V, int A, int B, int F3>
+__device__ __forceinline__ void conv_last_pass(const V* row0, int j, int ny, const V* twl, V* dst)
+{
+    constexpr int JS = 2 * A + 1;
+    if constexpr (F3) {
+        const V* src = row0 + j * JS;
+        V v[2][3][4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    V a = src[h * A + 3 * r + t];
+                    if (r > 0) a = cmulc_alt(a, twl[6 * r * j]);
+                    v[h][t][r] = a;
+                }
+                dft_reg<V, 4, true>(v[h][t]);
+            }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const V w1 = twl[2 * (j + B * r)], w2 = twl[4 * (j + B * r)];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                radix3_set<true>(v[h][0][r], v[h][1][r], v[h][2][r], w1, w2);
+#pragma unroll
+                for (int t = 0; t < 3; ++t) settle(v[h][t][r]);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int y = j + B * (r + 4 * t);
+                const V s = cadd(cmulc_set(v[1][t][r], twl[y]), v[0][t][r]);
+                if (y < ny) dst[y] = s;
+            }
+    } else {
+        const V* src = row0 + j;
+        V v[2][B];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int r = 0; r < B; ++r) {
+                v[h][r] = src[r * JS + h * A];
+                if (r) v[h][r] = cmulc_set(v[h][r], twl[2 * r * j]);
+            }
+            dft_reg<V, B, true>(v[h]);
+#pragma unroll
+            for (int r = 0; r < B; ++r) settle(v[h][r]);
+        }
+#pragma unroll
+        for (int r = 0; r < B; ++r) {
+            const int y = j + A * r;
+            const V s = cadd(cmulc_set(v[1][r], twl[y]), v[0][r]);
+            if (y < ny) dst[y] = s;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1223,41 +1347,7 @@ __global__ __launch_bounds__(conv1_cfg(BUILD, sizeof(T)).nt)
     }
     if ((int)threadIdx.x < G * 3 * B) {
         const int line = line1, j = j1;
-        V* dst = lines + line * LS + j * JS;
-        if constexpr (F3) {
-#pragma unroll
-            for (int a = 0; a < A; ++a) {
-                o[a] = cmul_set(e[a], twl[j + B * a]);
-                if (j + B * a >= ny) e[a] = o[a] = mk<V>(0, 0);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const V w1 = twl[2 * (j + B * r)], w2 = twl[4 * (j + B * r)];
-                radix3_set<false>(e[r], e[r + 4], e[r + 8], w1, w2);
-                radix3_set<false>(o[r], o[r + 4], o[r + 8], w1, w2);
-            }
-#pragma unroll
-            for (int t = 0; t < 3; ++t) {
-                V u[4], v[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) { u[r] = e[4 * t + r]; v[r] = o[4 * t + r]; }
-                dft_reg<V, 4, false>(u);
-                dft_reg<V, 4, false>(v);
-                // sub-line t, output k: column 3 k + t
-#pragma unroll
-                for (int k = 0; k < 4; ++k) { dst[3 * k + t] = u[k]; dst[A + 3 * k + t] = v[k]; }
-            }
-        } else {
-#pragma unroll
-            for (int a = 0; a < A; ++a) {
-                if (j + B * a >= ny) e[a] = mk<V>(0, 0);
-                o[a] = cmul_set(e[a], twl[j + B * a]);
-            }
-            dft_reg<V, A, false>(e);
-            dft_reg<V, A, false>(o);
-#pragma unroll
-            for (int a = 0; a < A; ++a) { dst[a] = e[a]; dst[A + a] = o[a]; }
-        }
+        conv_first_pass<V, A, B, F3>(e, o, j, ny, twl, lines + line * LS + j * JS);
     }
     __syncthreads();
 
@@ -1350,61 +1440,124 @@ __global__ __launch_bounds__(conv1_cfg(BUILD, sizeof(T)).nt)
     constexpr int N3 = F3 ? B : A;
     for (int it = threadIdx.x; it < G * 3 * N3; it += NT) {
         const int line = it / N3, j = it & (N3 - 1), g = line / 3;
-        V* dst = x0 + g * istr + (line - 3 * g) * ny;
-        if constexpr (F3) {
-            const V* src = lines + line * LS + j * JS;
-            V v[2][3][4];
+        conv_last_pass<V, A, B, F3>(lines + line * LS, j, ny, twl, x0 + g * istr + (line - 3 * g) * ny);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_convz: the convolution of several layers in place, for G images of one
+// kx, where both halves of the padded y spectrum of a slice fit in LDS together
+// (k_conv otherwise).  As k_conv1, every pass is spread over all threads as
+// items of a few values in registers, with workgroup barriers between them:
+// first pass of both halves from global memory, second pass, z-phase per
+// column, first inverse pass, last inverse pass of both halves joined onto
+// the slice.  So X crosses global memory once each way and no wavefront idles
+// through a pass, where k_conv takes the halves one after another, reads X
+// twice, adds to X' and gives a slice's few groups of lines to two or three
+// of its four wavefronts.  Operations and their order are k_conv's (FP64: up to
+// the rows of the kernel spectrum read for their mirrors).  Measured, us a
+// launch, k_conv -> k_convz: FP32 200 x 180 x 5, 20 images 244 -> 154; 128 x
+// 128 x 8, 20 images 133 -> 69; 60 x 44 x 2, 12 images 18.8 -> 9.7; FP64 128 x
+// 128 x 4, 32 images 182 -> 98; 100 x 75 x 3, 24 images 79 -> 51.  At 80 KiB
+// of LDS a slice, two workgroups to a CU, it is still the faster: FP32 180 x
+// 180 x 8, 20 images 227 -> 177; FP64 90 x 90 x 8 203 -> 81.  Bound by vector
+// arithmetic, LDS and, at 8 layers, registers.
+// LDS: (twiddles W_{2m}) + 3 nz G lines of B rows of 2A (+1) values; value
+// (row r, column q) of half h is first-pass output q of input j = r, then
+// frequency q + A r (12 r + q for 3 2^a lengths).
+// ---------------------------------------------------------------------------
+template <typename T, int MZ, int BUILD>
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 2, 8))) void k_convz(const Prob* __restrict__ P, int np,
+                                                                               const int* __restrict__ wstart,
+                                                                               cplx<T>* __restrict__ X,
+                                                                               const T* __restrict__ nhat,
+                                                                               const cplx<T>* __restrict__ tw,
+                                                                               const int* __restrict__ done)
+{
+    using V = cplx<T>;
+    constexpr Conv1Cfg C = conv1_cfg(BUILD, sizeof(T));
+    constexpr int A = C.A, B = C.B, MY = A * B, JS = 2 * A + 1, LS = conv1_line(C);
+    constexpr int F3 = BUILD >= 16, LMY = F3 ? BUILD - 16 : BUILD, TWL = convz_twlds(BUILD, sizeof(T));
+    extern __shared__ double2 smem_[];
+    const int pi = find_problem(wstart, np, blockIdx.x);
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
+    const int w = blockIdx.x - w0;
+    // workgroups as in k_conv1
+    const int nwk = (p.K + p.gconv - 1) / p.gconv;
+    const int kx = ((w >> 3) / nwk) * 8 + (w & 7), img0 = ((w >> 3) % nwk) * p.gconv;
+    if (kx > p.mx) return;
+    const int G = min(p.gconv, p.K - img0);
+    const int ny = p.ny, m1 = p.mx + 1, L = 3 * p.nz, nl = G * L;
+    V* lines = reinterpret_cast<V*>(smem_) + (TWL ? 2 * MY : 0);
+    const V* const twl = TWL ? reinterpret_cast<const V*>(smem_) : tw + tw_off(LMY, F3);
+    V* const x0 = X + p.x_off + ((long long)img0 * m1 + kx) * L * ny;
+    const long long istr = (long long)m1 * L * ny;
+    if constexpr (TWL) load_twiddles(reinterpret_cast<V*>(smem_), LMY, F3, tw);
+    __syncthreads();
+
+    // first pass: item (line, j), inputs j + B a; F3: y = j + B (r + 4 t)
+    for (int it = threadIdx.x; it < nl * B; it += kNT) {
+        const int line = it / B, j = it & (B - 1), g = line / L;
+        const V* src = x0 + g * istr + (line - L * g) * ny;
+        V e[A], o[A];
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+        for (int a = 0; a < A; ++a) e[a] = src[min(j + B * a, ny - 1)];
+        conv_first_pass<V, A, B, F3>(e, o, j, ny, twl, lines + line * LS + j * JS);
+    }
+    __syncthreads();
+
+    // second pass, in place: item (line, half, q), rows j of column q
+    for (int it = threadIdx.x; it < nl * 2 * A; it += kNT) {
+        const int line = it / (2 * A), hq = it - line * (2 * A), q = hq < A ? hq : hq - A;
+        V* col = lines + line * LS + hq;
+        const int k = F3 ? 3 * (q / 3) : q;  // twiddle of row j: W_{2m}^{2 j k}
+        V v[B];
 #pragma unroll
-                for (int t = 0; t < 3; ++t) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        V a = src[h * A + 3 * r + t];
-                        if (r > 0) a = cmulc_alt(a, twl[6 * r * j]);
-                        v[h][t][r] = a;
-                    }
-                    dft_reg<V, 4, true>(v[h][t]);
-                }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const V w1 = twl[2 * (j + B * r)], w2 = twl[4 * (j + B * r)];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    radix3_set<true>(v[h][0][r], v[h][1][r], v[h][2][r], w1, w2);
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) settle(v[h][t][r]);
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < 3; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int y = j + B * (r + 4 * t);
-                    const V s = cadd(cmulc_set(v[1][t][r], twl[y]), v[0][t][r]);
-                    if (y < ny) dst[y] = s;
-                }
-        } else {
-            const V* src = lines + line * LS + j;
-            V v[2][B];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-#pragma unroll
-                for (int r = 0; r < B; ++r) {
-                    v[h][r] = src[r * JS + h * A];
-                    if (r) v[h][r] = cmulc_set(v[h][r], twl[2 * r * j]);
-                }
-                dft_reg<V, B, true>(v[h]);
-#pragma unroll
-                for (int r = 0; r < B; ++r) settle(v[h][r]);
-            }
-#pragma unroll
-            for (int r = 0; r < B; ++r) {
-                const int y = j + A * r;
-                const V s = cadd(cmulc_set(v[1][r], twl[y]), v[0][r]);
-                if (y < ny) dst[y] = s;
-            }
+        for (int j = 0; j < B; ++j) {
+            v[j] = col[j * JS];
+            if (j) v[j] = cmul_set(v[j], twl[2 * j * k]);
         }
+        dft_reg<V, B, false>(v);
+#pragma unroll
+        for (int j = 0; j < B; ++j) col[j * JS] = v[j];
+    }
+    __syncthreads();
+
+    // z-phase: item (slice, half, frequency)
+    for (int it = threadIdx.x; it < G * 2 * MY; it += kNT) {
+        const int gh = it / MY, f = it - gh * MY, hy = gh & 1, r = f / A, q = f - r * A;
+        conv_zcolumn<T, MZ, LMY, F3, true, (MZ == 8 && MY < 256)>(p, kx, hy, f, lines + (gh >> 1) * L * LS + r * JS + hy * A + q, LS, nhat, tw);
+    }
+    __syncthreads();
+
+    // first inverse pass.  F3: in place, rows of column q; else item (line,
+    // half, q < B), frequencies q + B i to row q (the lanes of one line and
+    // half lie in one wavefront, which reads them all before it writes)
+    constexpr int R = F3 ? B : A, Q = F3 ? 12 : B;
+    for (int it = threadIdx.x; it < nl * 2 * Q; it += kNT) {
+        const int line = it / (2 * Q), hq = it - line * (2 * Q), h = hq < Q ? 0 : 1, q = hq - h * Q;
+        V* base = lines + line * LS + h * A;
+        V v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = F3 ? base[r * JS + q] : base[(r / (A / B)) * JS + q + B * (r % (A / B))];
+        dft_reg<V, R, true>(v);
+        wave_sync();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if constexpr (F3) base[r * JS + q] = v[r];
+            else base[q * JS + r] = v[r];
+        }
+    }
+    __syncthreads();
+
+    // last inverse pass of both halves, joined onto the slice
+    constexpr int N3 = F3 ? B : A;
+    for (int it = threadIdx.x; it < nl * N3; it += kNT) {
+        const int line = it / N3, j = it & (N3 - 1), g = line / L;
+        conv_last_pass<V, A, B, F3>(lines + line * LS, j, ny, twl, x0 + g * istr + (line - L * g) * ny);
     }
 }
 
@@ -2886,14 +3039,25 @@ template <typename T, int MZ, int BUILD>
 static void launch_conv_b(const Prob* P, int np, const WorkMap* wm, cplx<T>* x, const T* nhat, const cplx<T>* t,
                           const int* done, size_t lds, hipStream_t st)
 {
-    const WorkMap& w = wm[conv_slot(BUILD)];
-    if (!w.total) return;
-    if constexpr (MZ == 1 && BUILD > 0)
-        hipLaunchKernelGGL((k_conv1<T, BUILD>), dim3(w.total), dim3(conv1_cfg(BUILD, sizeof(T)).nt), w.lds, st, P, np,
-                           w.start, x, nhat, t, done);
-    else
-        hipLaunchKernelGGL((k_conv<T, MZ, BUILD>), dim3(w.total), dim3(kNT), lds, st, P, np, w.start, x, nhat, t,
-                           done);
+    // in place, both halves together
+    if constexpr (BUILD > 0) {
+        const WorkMap& w = wm[conv_slot(BUILD, 1)];
+        if (w.total) {
+            if constexpr (MZ == 1)
+                hipLaunchKernelGGL((k_conv1<T, BUILD>), dim3(w.total), dim3(conv1_cfg(BUILD, sizeof(T)).nt), w.lds,
+                                   st, P, np, w.start, x, nhat, t, done);
+            else if constexpr (conv_inplace_min(MZ, BUILD, sizeof(T)))
+                hipLaunchKernelGGL((k_convz<T, MZ, BUILD>), dim3(w.total), dim3(kNT), w.lds, st, P, np, w.start, x,
+                                   nhat, t, done);
+        }
+    }
+    // one half after the other
+    if constexpr (!conv_inplace_all(MZ, BUILD, sizeof(T))) {
+        const WorkMap& w = wm[conv_slot(BUILD, 0)];
+        if (w.total)
+            hipLaunchKernelGGL((k_conv<T, MZ, BUILD>), dim3(w.total), dim3(kNT), lds, st, P, np, w.start, x, nhat, t,
+                               done);
+    }
 }
 
 template <typename T, int MZ>

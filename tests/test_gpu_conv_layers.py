@@ -1,0 +1,42 @@
+"""The in-place convolution of several layers (k_convz) at the edges of its
+y lengths, for layer counts at both ends of a padded count and on both sides of
+the one where a slice no longer fits in LDS with both halves (k_conv then):
+fields against the oracle at 1e-10 (FP64) and 1e-5 (FP32-mixed), and bitwise
+the same whatever number of images a workgroup takes."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1804_07135_amd import inputs, ssm
+
+pytestmark = pytest.mark.gpu
+
+TOL = {ssm.SSM_FP64: 1e-10, ssm.SSM_FP32_MIXED: 1e-5}
+
+
+@pytest.mark.parametrize("precision", [ssm.SSM_FP64, ssm.SSM_FP32_MIXED])
+@pytest.mark.parametrize("ny,nz,K", [(17, 2, 5), (32, 8, 2), (33, 3, 7), (48, 4, 2), (49, 5, 3), (64, 2, 9), (65, 7, 2),
+                                     (96, 4, 3), (96, 8, 2), (97, 3, 3), (128, 4, 2), (128, 5, 2), (128, 7, 2),
+                                     (129, 2, 3), (191, 3, 2), (192, 4, 2), (192, 8, 2), (193, 2, 2), (255, 3, 2),
+                                     (256, 4, 2), (256, 5, 2), (250, 6, 2), (256, 7, 2)])
+def test_layered_lengths_vs_oracle(oracle, tmp_path, precision, ny, nz, K):
+    p = dict(nx=2, ny=ny, nz=nz, K=K, J=0.9, d=0.35, ku=0.21, D=0.4)
+    s = inputs.random_unit_spins((K, 3, nz, ny, 2), seed=ny + nz)
+    if precision == ssm.SSM_FP32_MIXED:
+        s = s.astype(np.float32).astype(np.float64)
+    sm = ssm.StringMethod(p, precision)
+    h = sm.eval(s)[1]
+    for k in (0, K - 1):
+        ho = oracle.field(s[k], p["J"], p["d"], p["ku"], p["D"])
+        assert np.abs(h[k].cpu().numpy() - ho).max() < TOL[precision] * np.abs(ho).max(), k
+    dev = torch.cuda.get_device_properties(0).gcnArchName.replace(" ", "_")
+    sm.set_string(s)
+    for g in (1, 2, 3):
+        cache = tmp_path / f"tiles{g}"
+        cache.write_text(f"{dev} {precision} 2x{ny}x{nz} {K} 8 4 {g}\n")
+        try:
+            sm.autotune(str(cache))
+        except ssm.SSMError as e:  # more slices than fit (the half-by-half kernel takes what it is given)
+            assert e.status == ssm.SSM_EUNSUPPORTED
+            continue
+        assert torch.equal(sm.eval(s)[1], h), g
