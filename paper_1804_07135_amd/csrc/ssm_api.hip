@@ -332,13 +332,14 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         p.nhz = q.nz > 1 ? 2 : 1;
         p.N = (long long)q.nx * q.ny * q.nz;
         p.conv1 = conv_inplace(p.nz, p.mz, conv_build(p.mz, p.lmy, p.f3y), (int)pl.tsize);
-        // one component per forward x workgroup until a launch has 4096
-        // tiles (of about 4096 elements) without it: shorter chains and more
-        // workgroups (64 x 64, 20 images, FP32: 11.0 -> 7.8 us; 64 lattices
-        // of 72 x 72, 16 images: 76 -> 68; 200 x 180 x 5, 20 images: 50 ->
-        // 45); beyond that the twiddle loads and barriers it repeats cost
-        // more (256 x 256 x 8, 48 images: 181 -> 189, FP64 390 -> 415)
-        p.csplit = batch_rows * p.mx < (1 << 24) ? 1 : 0;
+        // one component per forward x workgroup on small launches: shorter
+        // chains and more workgroups (64 x 64, 20 images, FP32: 11.0 -> 7.4
+        // us; 250 x 250 x 3, 20 images: 43 -> 37; with the longer chain of
+        // lengths 3 2^a still 64 lattices of 72 x 72, 16 images: 76 -> 67);
+        // on larger ones the twiddle loads and barriers it repeats cost more
+        // (256 x 256 x 4, 32 images: 63 -> 68; 256 x 256 x 8, 48 images: 181
+        // -> 189, FP64 390 -> 415)
+        p.csplit = batch_rows * p.mx < (p.f3x ? 1 << 24 : 1 << 22) ? 1 : 0;
         const Tiles t = tiles ? (*tiles)[i] : default_tiles(p, pl.tsize, batch_rows, batch_slices);
         apply_tiles(p, t, pl.tsize);
         pl.tiles.push_back(t);
