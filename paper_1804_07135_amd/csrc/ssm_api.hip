@@ -268,7 +268,8 @@ void apply_tiles(Prob& p, const Tiles& t, size_t tsize)
     size_t lds;
     p.xi2 = xinv2_tile(p, p.yt, tsize, lds) ? 1 : 0;
     p.gconv = t.gconv;
-    p.xcd_remap = (t.gconv == 1) ? 1 : 0;
+    if (!p.conv1 && conv_halves(p.mz, conv_build(p.mz, p.lmy, p.f3y), (int)tsize)) p.gconv = 1;  // k_convh
+    p.xcd_remap = (p.gconv == 1) ? 1 : 0;
     if (p.conv1) {
         // at most what the build's LDS holds, and the images of a kx spread
         // evenly over its workgroups

@@ -94,6 +94,20 @@ __host__ __device__ constexpr size_t convz_lds(int build, int G, int nz, int tsi
     return (size_t)((convz_twlds(build, tsize) ? 2 * c.A * c.B : 0) + G * 3 * nz * conv1_line(c)) * 2 * tsize;
 }
 
+// k_convh (FP64, 4 padded layers, one half at a time, one slice to a
+// workgroup): where it serves the slices that k_convz doesn't hold, and LDS for
+// up to nz layers
+__host__ __device__ constexpr bool conv_halves(int mz, int build, int tsize)
+{
+    return tsize == 8 && mz == 4 && build > 0;
+}
+__host__ __device__ constexpr int convh_line(Conv1Cfg c) { return c.B * (c.A + 1); }
+__host__ __device__ constexpr size_t convh_lds(int build, int nz)
+{
+    const Conv1Cfg c = conv1_cfg(build, 8);
+    return (size_t)(2 * c.A * c.B + 3 * nz * convh_line(c)) * 16;
+}
+
 // Whether the in-place kernels take a problem: monolayers always; several
 // layers where one slice's lines of both halves fit kConvzLds: two workgroups
 // to a CU, where it was measured the faster; one to a CU would hold fewer

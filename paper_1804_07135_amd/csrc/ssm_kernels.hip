@@ -1561,6 +1561,175 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     }
 }
 
+// ---------------------------------------------------------------------------
+// k_convh: the FP64 convolution of 3 or 4 layers at the y lengths whose lines
+// of both halves k_convz can't hold (192 with 4 layers, and 256): one half of
+// the padded y spectrum after the other, as k_conv (half 1 is added onto what
+// half 0 left in X'), its passes spread over all threads as in k_convz.
+// Bound by latency at two wavefronts to a SIMD (256 VGPRs, a slice's lines of
+// one half in up to 59 KiB of LDS): passes of one item per thread keep a few
+// values each and have no line groups half of which idle, where k_conv's
+// wavefronts hold 16 values a lane for whole lines.  Images of 250x250x3,
+// 20 of them: 208 us against 370; 256x256x4, 32: 477 against 638; 180x180x4,
+// 20: 171 against 197.  With 8 padded layers (112 KiB: one workgroup of 512 to
+// a CU, only half of whose threads hold a z column) 256x256x8, 48 took 2554 us
+// against 1687, 180x180x8, 20 582 against 568: k_conv keeps those.
+// LDS: twiddles W_{2m} + 3 nz lines of B rows of A (+1) values.
+// ---------------------------------------------------------------------------
+template <int MZ, int BUILD>
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_convh(
+    const Prob* __restrict__ P, int np, const int* __restrict__ wstart, double2* __restrict__ X,
+    const double* __restrict__ nhat, const double2* __restrict__ tw, const int* __restrict__ done)
+{
+    using V = double2;
+    constexpr Conv1Cfg C = conv1_cfg(BUILD, 8);
+    constexpr int A = C.A, B = C.B, MY = A * B, JS = A + 1, LS = convh_line(C), NT = kNT;
+    constexpr int F3 = BUILD >= 16, LMY = F3 ? BUILD - 16 : BUILD;
+    extern __shared__ double2 smem_[];
+    const int pi = find_problem(wstart, np, blockIdx.x);
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
+    const int w = blockIdx.x - w0;
+    // one slice; the images of one kx back to back on one XCD
+    const int kx = ((w >> 3) / p.K) * 8 + (w & 7), img = (w >> 3) % p.K;
+    if (kx > p.mx) return;
+    const int ny = p.ny, nl = 3 * p.nz;
+    V* const twl = smem_;
+    V* const lines = twl + 2 * MY;
+    const long long so = ((long long)img * (p.mx + 1) + kx) * nl * ny;
+    const V* const in = X + p.x_off + so;
+    V* const out = X + p.xo_off + so;
+    load_twiddles(twl, LMY, F3, tw);
+#pragma unroll 1
+    for (int hy = 0; hy < 2; ++hy) {
+        __syncthreads();
+        // first pass: item (line, j), inputs j + B a; F3: y = j + B (r + 4 t)
+        for (int it = threadIdx.x; it < nl * B; it += NT) {
+            const int line = it / B, j = it & (B - 1);
+            const V* src = in + line * ny;
+            V* dst = lines + line * LS + j * JS;
+            V e[A];
+#pragma unroll
+            for (int a = 0; a < A; ++a) e[a] = src[min(j + B * a, ny - 1)];
+#pragma unroll
+            for (int a = 0; a < A; ++a)
+                if (j + B * a >= ny) e[a] = mk<V>(0, 0);
+            if (hy) {
+#pragma unroll
+                for (int a = 0; a < A; ++a) e[a] = cmul_set(e[a], twl[j + B * a]);
+            }
+            if constexpr (F3) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    radix3_set<false>(e[r], e[r + 4], e[r + 8], twl[2 * (j + B * r)], twl[4 * (j + B * r)]);
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    V u[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) u[r] = e[4 * t + r];
+                    dft_reg<V, 4, false>(u);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) dst[3 * k + t] = u[k];
+                }
+            } else {
+                dft_reg<V, A, false>(e);
+#pragma unroll
+                for (int a = 0; a < A; ++a) dst[a] = e[a];
+            }
+        }
+        __syncthreads();
+
+        // second pass, in place: item (line, q), rows j of column q
+        for (int it = threadIdx.x; it < nl * A; it += NT) {
+            const int line = it / A, q = it - line * A;
+            V* col = lines + line * LS + q;
+            const int k = F3 ? 3 * (q / 3) : q;
+            V v[B];
+#pragma unroll
+            for (int j = 0; j < B; ++j) {
+                v[j] = col[j * JS];
+                if (j) v[j] = cmul_set(v[j], twl[2 * j * k]);
+            }
+            dft_reg<V, B, false>(v);
+#pragma unroll
+            for (int j = 0; j < B; ++j) col[j * JS] = v[j];
+        }
+        __syncthreads();
+
+        for (int f = threadIdx.x; f < MY; f += NT) {
+            const int r = f / A, q = f - r * A;
+            conv_zcolumn<double, MZ, LMY, F3, true, false>(p, kx, hy, f, lines + r * JS + q, LS, nhat, tw);
+        }
+        __syncthreads();
+
+        // first inverse pass (as in k_convz)
+        constexpr int R = F3 ? B : A, Q = F3 ? 12 : B;
+        for (int it = threadIdx.x; it < nl * Q; it += NT) {
+            const int line = it / Q, q = it - line * Q;
+            V* base = lines + line * LS;
+            V v[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r] = F3 ? base[r * JS + q] : base[(r / (A / B)) * JS + q + B * (r % (A / B))];
+            dft_reg<V, R, true>(v);
+            wave_sync();
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if constexpr (F3) base[r * JS + q] = v[r];
+                else base[q * JS + r] = v[r];
+            }
+        }
+        __syncthreads();
+
+        // last inverse pass: half 0 to X', half 1 un-twiddled and added to it
+        // (by the thread that stored it)
+        constexpr int N3 = F3 ? B : A, NO = F3 ? 12 : B;
+        for (int it = threadIdx.x; it < nl * N3; it += NT) {
+            const int line = it / N3, j = it & (N3 - 1);
+            V* dst = out + line * ny;
+            V v[NO];
+            if constexpr (F3) {
+                const V* src = lines + line * LS + j * JS;
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    V u[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        u[r] = src[3 * r + t];
+                        if (r > 0) u[r] = cmulc_set(u[r], twl[6 * r * j]);
+                    }
+                    dft_reg<V, 4, true>(u);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[4 * t + r] = u[r];
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    radix3_set<true>(v[r], v[4 + r], v[8 + r], twl[2 * (j + B * r)], twl[4 * (j + B * r)]);
+            } else {
+                const V* src = lines + line * LS + j;
+#pragma unroll
+                for (int r = 0; r < B; ++r) {
+                    v[r] = src[r * JS];
+                    if (r) v[r] = cmulc_set(v[r], twl[2 * r * j]);
+                }
+                dft_reg<V, B, true>(v);
+            }
+            constexpr int YS = F3 ? B : A;  // output o at y = j + YS o
+            if (hy) {
+                V h0[NO];
+#pragma unroll
+                for (int o = 0; o < NO; ++o) h0[o] = dst[min(j + YS * o, ny - 1)];
+#pragma unroll
+                for (int o = 0; o < NO; ++o) v[o] = cadd(cmulc_set(v[o], twl[j + YS * o]), h0[o]);
+            }
+#pragma unroll
+            for (int o = 0; o < NO; ++o)
+                if (j + YS * o < ny) dst[j + YS * o] = v[o];
+        }
+    }
+}
+
 // The value of the next (previous) lane of the wavefront: DPP wavefront
 // shifts by one lane (one VALU move, no LDS permute); the last (first) lane
 // receives 0, which callers replace.
@@ -3054,7 +3223,11 @@ static void launch_conv_b(const Prob* P, int np, const WorkMap* wm, cplx<T>* x, 
     // one half after the other
     if constexpr (!conv_inplace_all(MZ, BUILD, sizeof(T))) {
         const WorkMap& w = wm[conv_slot(BUILD, 0)];
-        if (w.total)
+        if (!w.total) return;
+        if constexpr (conv_halves(MZ, BUILD, sizeof(T)))
+            hipLaunchKernelGGL((k_convh<MZ, BUILD>), dim3(w.total), dim3(kNT), convh_lds(BUILD, MZ), st, P, np,
+                               w.start, x, nhat, t, done);
+        else
             hipLaunchKernelGGL((k_conv<T, MZ, BUILD>), dim3(w.total), dim3(kNT), lds, st, P, np, w.start, x, nhat, t,
                                done);
     }

@@ -40,3 +40,21 @@ def test_layered_lengths_vs_oracle(oracle, tmp_path, precision, ny, nz, K):
             assert e.status == ssm.SSM_EUNSUPPORTED
             continue
         assert torch.equal(sm.eval(s)[1], h), g
+
+
+@pytest.mark.parametrize("ny,nz", [(129, 4), (161, 4), (193, 3), (193, 4), (241, 4), (256, 3)])
+def test_halves_kernel_edges(oracle, ny, nz):
+    """FP64, 3 and 4 layers at the y lengths of the half-by-half kernel of one
+    slice per workgroup (k_convh): shortest, ragged and longest lines, an odd
+    number of x columns and of images, alone and beside another problem."""
+    p = dict(nx=3, ny=ny, nz=nz, K=3, J=0.9, d=0.35, ku=0.21, D=0.4)
+    s = inputs.random_unit_spins((3, 3, nz, ny, 3), seed=ny * nz)
+    h = ssm.StringMethod(p, ssm.SSM_FP64).eval(s)[1]
+    for k in range(3):
+        ho = oracle.field(s[k], p["J"], p["d"], p["ku"], p["D"])
+        assert np.abs(h[k].cpu().numpy() - ho).max() < 1e-10 * np.abs(ho).max(), k
+    q = dict(p, ny=200, K=2)
+    s2 = inputs.random_unit_spins((2, 3, nz, 200, 3), seed=1)
+    both = ssm.StringMethod([q, p], ssm.SSM_FP64)
+    hb = both.eval(torch.cat([torch.as_tensor(s2).reshape(-1), torch.as_tensor(s).reshape(-1)]))[1]
+    assert torch.equal(hb.reshape(-1)[-h.numel():].cpu(), h.reshape(-1).cpu())
