@@ -23,9 +23,9 @@ namespace {
 constexpr int kVersion = 1;
 constexpr size_t kAlign = 256;
 constexpr size_t kLdsMax = 160 * 1024;
-// work maps: forward / inverse x per length kind (2 + 2), convolution per
+// work maps: forward / inverse x per kind (2 + 3), convolution per
 // build slot, arc, site, image, per-problem site, 4-site
-constexpr int kNumMaps = 4 + kConvSlots + 5;
+constexpr int kNumMaps = 5 + kConvSlots + 5;
 
 thread_local std::string g_create_error;
 
@@ -104,12 +104,12 @@ struct Plan {
     std::vector<int> geo;             // problem -> distinct-shape index
     std::vector<std::tuple<int, int, int>> shapes;
     std::vector<long long> nh_size;   // elements per distinct shape
-    std::vector<int> wm_xf[2], wm_xi[2], wm_conv[kConvSlots];  // per kind
+    std::vector<int> wm_xf[2], wm_xi[3], wm_conv[kConvSlots];  // per kind
     std::vector<int> wm_arc, wm_site, wm_img, wm_sitep, wm_site4;
     // n_x, n_xp: complex values of the x half-spectra X and of the convolved
     // ones X' kept apart from them (problems not convolved in place)
     long long n_img = 0, n_spin = 0, n_x = 0, n_xp = 0, n_nh = 0, n_ep = 0, n_ap = 0, n_fp = 0, n_fm = 0;
-    size_t lds_xf = 0, lds_xi[2] = {}, lds_conv = 0, lds_conv1[kConvSlots] = {};
+    size_t lds_xf = 0, lds_xi[3] = {}, lds_conv = 0, lds_conv1[kConvSlots] = {};
     size_t scratch_bytes = 0;
     // workspace offsets
     size_t o_P, o_wm, o_tw, o_tw64, o_s, o_ss, o_h, o_nh, o_big, o_ep, o_ap, o_fp, o_E, o_T,
@@ -154,7 +154,7 @@ bool xinv2_tile(const Prob& p, int yt, size_t tsize, size_t& lds)
     if (!xinv2_len(p.lmx, p.f3x, (int)tsize)) return false;
     const Xinv2 c = xinv2_cfg(p.lmx, p.f3x);
     const int hp = yt / 2;
-    if (3 * hp * c.r1 > xinv2_rounds(c) * kNT) return false;
+    if (3 * hp * c.r1 > xinv2_rounds(c, kNT) * kNT) return false;
     const size_t lines = (size_t)3 * hp * xinv2_line(c, hp, (int)tsize) * 2 * tsize;
     const size_t field = (size_t)3 * yt * xinv2_hrow(p.nx, hp) * tsize;
     lds = std::max(lines, field) + (xinv2_twlds(p.mx, p.f3x, (int)tsize) ? 4 * p.mx * tsize : 0);
@@ -266,7 +266,7 @@ void apply_tiles(Prob& p, const Tiles& t, size_t tsize)
     p.tiles = p.nz * p.nty;
     p.wgi = pad8(p.K * p.tiles);
     size_t lds;
-    p.xi2 = xinv2_tile(p, p.yt, tsize, lds) ? 1 : 0;
+    p.xi2 = !xinv2_tile(p, p.yt, tsize, lds) ? 0 : xinv2_wide(p.lmx, p.f3x, (int)tsize) ? 2 : 1;
     p.gconv = t.gconv;
     if (!p.conv1 && conv_halves(p.mz, conv_build(p.mz, p.lmy, p.f3y), (int)tsize)) p.gconv = 1;  // k_convh
     p.xcd_remap = (p.gconv == 1) ? 1 : 0;
@@ -279,6 +279,9 @@ void apply_tiles(Prob& p, const Tiles& t, size_t tsize)
         p.gconv = (p.K + n - 1) / n;
     }
 }
+
+// the inverse x transform's kind: x length kind, or the wide workgroups
+int xi_kind(const Prob& p) { return p.xi2 == 2 ? 2 : p.f3x; }
 
 int conv_wgs(const Prob& p)
 {
@@ -413,7 +416,8 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         pl.lds_xf = std::max(pl.lds_xf, lds_xfwd(p, p.ytf, pl.tsize));
         size_t lxi = lds_xinv(p, p.yt, pl.tsize);
         if (p.xi2) (void)xinv2_tile(p, p.yt, pl.tsize, lxi);
-        pl.lds_xi[p.f3x] = std::max(pl.lds_xi[p.f3x], lxi);
+        size_t& mxi = pl.lds_xi[xi_kind(p)];
+        mxi = std::max(mxi, lxi);
         size_t& lc = p.conv1 ? pl.lds_conv1[conv_slot(conv_build(p.mz, p.lmy, p.f3y), 1)] : pl.lds_conv;
         lc = std::max(lc, lds_convg(p, p.gconv, pl.tsize));
     }
@@ -442,8 +446,8 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
     // the FFT kernels per kind: other kinds' problems get no workgroups
     for (int k = 0; k < 2; ++k) {
         prefix(pl.wm_xf[k], [k](const Prob& p) { return p.f3x == k ? p.wgf : 0; });
-        prefix(pl.wm_xi[k], [k](const Prob& p) { return p.f3x == k ? p.wgi : 0; });
     }
+    for (int k = 0; k < 3; ++k) prefix(pl.wm_xi[k], [k](const Prob& p) { return xi_kind(p) == k ? p.wgi : 0; });
     for (int j = 0; j < kConvSlots; ++j)
         prefix(pl.wm_conv[j], [j](const Prob& p) {
             return conv_slot(conv_build(p.mz, p.lmy, p.f3y), p.conv1) == j ? (int)conv_wgs(p) : 0;
@@ -549,29 +553,29 @@ struct ssm_ctx {
         w.lds = 0;
         return w;
     }
-    struct XMaps { WorkMap m[2]; };
+    struct XMaps { WorkMap m[3]; };
     struct ConvMaps { WorkMap m[kConvSlots]; };
-    XMaps wm_xf() const { return {{wm(0, pl.wm_xf[0]), wm(1, pl.wm_xf[1])}}; }
+    XMaps wm_xf() const { return {{wm(0, pl.wm_xf[0]), wm(1, pl.wm_xf[1]), {}}}; }
     XMaps wm_xi() const
     {
-        XMaps r = {{wm(2, pl.wm_xi[0]), wm(3, pl.wm_xi[1])}};
-        for (int k = 0; k < 2; ++k) r.m[k].lds = pl.lds_xi[k];
+        XMaps r = {{wm(2, pl.wm_xi[0]), wm(3, pl.wm_xi[1]), wm(4, pl.wm_xi[2])}};
+        for (int k = 0; k < 3; ++k) r.m[k].lds = pl.lds_xi[k];
         return r;
     }
     ConvMaps wm_conv() const
     {
         ConvMaps r;
         for (int j = 0; j < kConvSlots; ++j) {
-            r.m[j] = wm(4 + j, pl.wm_conv[j]);
+            r.m[j] = wm(5 + j, pl.wm_conv[j]);
             r.m[j].lds = pl.lds_conv1[j];
         }
         return r;
     }
-    WorkMap wm_arc() const { return wm(4 + kConvSlots, pl.wm_arc); }
-    WorkMap wm_site() const { return wm(5 + kConvSlots, pl.wm_site); }
-    WorkMap wm_img() const { return wm(6 + kConvSlots, pl.wm_img); }
-    WorkMap wm_sitep() const { return wm(7 + kConvSlots, pl.wm_sitep); }
-    WorkMap wm_site4() const { return wm(8 + kConvSlots, pl.wm_site4); }
+    WorkMap wm_arc() const { return wm(5 + kConvSlots, pl.wm_arc); }
+    WorkMap wm_site() const { return wm(6 + kConvSlots, pl.wm_site); }
+    WorkMap wm_img() const { return wm(7 + kConvSlots, pl.wm_img); }
+    WorkMap wm_sitep() const { return wm(8 + kConvSlots, pl.wm_sitep); }
+    WorkMap wm_site4() const { return wm(9 + kConvSlots, pl.wm_site4); }
     Step2 step2() const
     {
         Step2 r;
@@ -956,7 +960,8 @@ static ssm_status upload_plan(ssm_ctx* c)
     HIPCHK(c, hipMemcpyAsync(c->ws + pl.o_P, pl.P.data(), sizeof(Prob) * pl.np,
                              hipMemcpyHostToDevice, c->stream), "upload descriptors");
     std::vector<int> wm;
-    std::vector<const std::vector<int>*> maps = {&pl.wm_xf[0], &pl.wm_xf[1], &pl.wm_xi[0], &pl.wm_xi[1]};
+    std::vector<const std::vector<int>*> maps = {&pl.wm_xf[0], &pl.wm_xf[1], &pl.wm_xi[0], &pl.wm_xi[1],
+                                               &pl.wm_xi[2]};
     for (int j = 0; j < kConvSlots; ++j) maps.push_back(&pl.wm_conv[j]);
     for (const auto* v : {&pl.wm_arc, &pl.wm_site, &pl.wm_img, &pl.wm_sitep, &pl.wm_site4}) maps.push_back(v);
     for (const auto* v : maps) wm.insert(wm.end(), v->begin(), v->end());

@@ -182,8 +182,13 @@ __host__ __device__ constexpr Xinv2 xinv2_cfg(int lm, int f3)
     const int m = (f3 ? 3 : 1) << lm, r1 = lm == 5 ? 8 : 16;
     return Xinv2{r1, m / r1, m / r1};
 }
-// its rounds of second-step items per thread (tiles of at most 2048 elements)
-__host__ __device__ constexpr int xinv2_rounds(Xinv2 c) { return (12 + c.nout - 1) / c.nout; }
+// its rounds of second-step items per thread (tiles of at most 2048 elements
+// and workgroups of nt threads)
+__host__ __device__ constexpr int xinv2_rounds(Xinv2 c, int nt)
+{
+    const int per = c.nout * (nt / 256);
+    return (12 + per - 1) / per;
+}
 // LDS elements from one row pair to the next: nb rows of 2 r1 + 1 values, made
 // an odd multiple of what spreads hp row pairs (consecutive lanes) over the
 // banks
@@ -192,6 +197,22 @@ __host__ __device__ constexpr int xinv2_line(Xinv2 c, int hp, int tsize)
     const int n = c.nb * (2 * c.r1 + 1), w = tsize == 4 ? 32 : 16, u = hp < w ? w / hp : 1;
     const int k = (n + u - 1) / u;
     return u * (k | 1);
+}
+// Threads of the inverse x transform's workgroups, and the lengths with such
+// workgroups (Prob::xi2 = 2, in two steps), whose lattices have the fewest
+// tiles: twice the wavefronts halve each lane's chain of rows where few
+// workgroups share a CU.  k_xinv, us, 256 -> 512 threads: FP32 64 x 64, 20
+// images 16.4 -> 13.2, 200 20.6 -> 18.8, 1000 57 -> 60; 32 x 32, 10 images
+// 12.0 -> 10.8; FP64 32 x 32, 10 images 13.0 -> 11.3, 1000 30.8 -> 29.9.  Longer
+// lines lose on large batches what they gain on small ones (FP32 112 x 112,
+// 60 images 20.6 -> 18.9 but 240 50.8 -> 54.1; 72 x 72, 1000 107 -> 125; 256 x
+// 256 x 8, 48 images 413 -> 470; FP64 64 x 64, 1000 92 -> 117), and the choice is
+// the problem's alone, since the order of its energy sums follows from it.
+// 1024 threads: 64 x 64, 1000 images 87.
+constexpr int kXinvWide = 512;
+__host__ __device__ constexpr bool xinv2_wide(int lm, int f3, int tsize)
+{
+    return !f3 && lm <= (tsize == 4 ? 6 : 5);
 }
 // row stride of the tile's real field, likewise
 __host__ __device__ constexpr int xinv2_hrow(int nx, int hp)
@@ -229,7 +250,7 @@ struct Prob {
     int gconv;             // (image, kx) slices per convolution workgroup: consecutive ones (kx fastest),
                            // or images of one kx (monolayers)
     int conv1;             // convolution in place, both halves together: 1 by k_conv1, 2 by k_convz
-    int xi2;               // 1: inverse x transform by xinv_two_step
+    int xi2;               // inverse x transform by xinv_two_step: 1, or 2 with kXinvWide threads
     int arc_chunks;        // arc-length workgroups (flat chunks of 3N) per image
     int xcd_remap;         // convolution kernel: group same-kx slices on one XCD
     long long N;           // sites per image
@@ -266,7 +287,8 @@ struct WorkMap {
 // convolution: one build per conv_build value) and each kind has a work map
 // of its own, in which the problems of other kinds have no workgroups; a
 // kind whose map is empty is not launched.  wm[0..1]: x length kinds
-// (f3x); wm[conv_slot(b)]: convolution build b.
+// (f3x), inverse x also wm[2] (Prob::xi2 = 2); wm[conv_slot(b)]: convolution
+// build b.
 // (the in-place kernels have slots of their own, kConvSlots / 2 further on)
 constexpr int kConvSlots = 16;
 __host__ __device__ constexpr int conv_slot(int b, int inplace)

@@ -1863,7 +1863,7 @@ __device__ __forceinline__ void xinv_load_lines(const char* __restrict__ Xi, cpl
 // 136 -> 114; 112 x 112, 60 images, FP32 23.4 -> 18.7 and 240 images 59 ->
 // 47; 256 x 256 x 8, 48 images, FP32 441 -> 405; 128 x 128 x 4, 32 images,
 // FP64 68 -> 56; 32 x 32, 10 images, FP64 18.3 -> 12.9.
-template <typename T, int F3, int LM>
+template <typename T, int F3, int LM, int NT>
 __device__ __forceinline__ void xinv_two_step(const char* __restrict__ Xi, cplx<T>* lines, T* hd,
                                               const cplx<T>* twl_lds, const cplx<T>* __restrict__ tw, int z, int y0,
                                               int hp, int lhp, int nx, int nz, int ny, int hrow)
@@ -1871,7 +1871,7 @@ __device__ __forceinline__ void xinv_two_step(const char* __restrict__ Xi, cplx<
     using V = cplx<T>;
     constexpr Xinv2 C = xinv2_cfg(LM, F3);
     constexpr int R1 = C.r1, NB = C.nb, NO = C.nout, RS = 2 * R1 + 1, m = (F3 ? 3 : 1) << LM;
-    constexpr int TR = xinv2_rounds(C);
+    constexpr int TR = xinv2_rounds(C, NT);
     const V* twl;
     if constexpr (xinv2_twlds(m, F3, sizeof(T))) twl = twl_lds;
     else twl = tw + tw_off(LM, F3);
@@ -1880,7 +1880,7 @@ __device__ __forceinline__ void xinv_two_step(const char* __restrict__ Xi, cplx<
     const bool odd = ny & 1;
     // step 1: item (rp, i, half h, component c)
 #pragma unroll 1
-    for (int it = threadIdx.x; it < 6 * NB * hp; it += kNT) {
+    for (int it = threadIdx.x; it < 6 * NB * hp; it += NT) {
         const int rp = it & (hp - 1), q = it >> lhp, ch = q / NB, i = q - ch * NB, h = ch & 1, c = ch >> 1;
         const int ya = y0 + 2 * rp, k0 = 2 * i + h;
         // frequency k0 + 2 NB r directly for r < R1 / 2 (and r = R1 / 2 where
@@ -1931,7 +1931,7 @@ __device__ __forceinline__ void xinv_two_step(const char* __restrict__ Xi, cplx<
     V out[TR][NO];
 #pragma unroll
     for (int u = 0; u < TR; ++u) {
-        const int it = threadIdx.x + u * kNT;
+        const int it = threadIdx.x + u * NT;
         if (it < n2) {
             const int rp = it & (hp - 1), q = it >> lhp, k = q & (R1 - 1), c = q / R1;
             const V* src = lines + (c * hp + rp) * LS + k;
@@ -1990,7 +1990,7 @@ __device__ __forceinline__ void xinv_two_step(const char* __restrict__ Xi, cplx<
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < TR; ++u) {
-        const int it = threadIdx.x + u * kNT;
+        const int it = threadIdx.x + u * NT;
         if (it < n2) {
             const int rp = it & (hp - 1), q = it >> lhp, k = q & (R1 - 1), c = q / R1;
             T* dst = hd + (2 * (c * hp + rp)) * hrow;
@@ -2016,9 +2016,10 @@ __device__ __forceinline__ void xinv_two_step(const char* __restrict__ Xi, cplx<
 // in the real part and row b in the imaginary part.
 // LDS: twiddles (2m) + yt lines of m + the tile's dipolar field (3 yt nx); with
 // xinv_two_step the lines of all components, and the field over them.
+// NT threads: kNT, or kXinvWide (the problems with xi2 = 2).
 // ---------------------------------------------------------------------------
-template <typename T, int F3>
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? SSM_XINV_WAVES_F32 : 3, 8))) void k_xinv(const Prob* __restrict__ P, int np,
+template <typename T, int F3, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT > kNT ? 4 : sizeof(T) == 4 ? SSM_XINV_WAVES_F32 : 3, 8))) void k_xinv(const Prob* __restrict__ P, int np,
                                               const int* __restrict__ wstart,
                                               const cplx<T>* __restrict__ Xp,
                                               const T* __restrict__ s, T* __restrict__ ss,
@@ -2029,13 +2030,13 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 {
     using V = cplx<T>;
     extern __shared__ double2 smem_[];
-    __shared__ double red[kNT / 64][kNTerm];
+    __shared__ double red[NT / 64][kNTerm];
     const int pi = find_problem(wstart, np, blockIdx.x);
     int w0;
     bool off;
     const Prob& p = problem(P, pi, wstart, done, w0, off);
     if (off) return;
-    if (p.f3x != F3) return;  // served by the other length kind's launch
+    if (p.f3x != F3 || (p.xi2 == 2) != (NT > kNT)) return;  // served by another kind's launch
     const int t = xcd_item(blockIdx.x - w0, p.wgi);
     if (t >= p.K * p.tiles) return;
     // z fastest: the tiles that read a plane's rows as z neighbours run
@@ -2058,7 +2059,9 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     // the tile's dipolar field, rows of stride hrow
     T* hd;
     int hrow;
-    if (p.xi2) {
+    bool two = true;
+    if constexpr (NT == kNT) two = p.xi2;
+    if (two) {
         const bool tl = xinv2_twlds(m, f3, sizeof(T));
         if (tl) load_twiddles(twl, lm, f3, tw);
         else lines = twl;
@@ -2066,7 +2069,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
         hrow = xinv2_hrow(nx, hp);
         auto run = [&](auto lmc) {
             constexpr int LM = decltype(lmc)::value;
-            xinv_two_step<T, F3, LM>(Xi, lines, hd, twl, tw, z, y0, hp, lhp, nx, nz, ny, hrow);
+            if constexpr (NT > kNT ? !F3 && (LM == 5 || (LM == 6 && sizeof(T) == 4)) : true)
+                xinv_two_step<T, F3, LM, NT>(Xi, lines, hd, twl, tw, z, y0, hp, lhp, nx, nz, ny, hrow);
         };
         switch (lm) {
         case 4: if constexpr (F3) run(std::integral_constant<int, 4>{}); break;
@@ -2075,7 +2079,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
         case 7: if constexpr (!F3) run(std::integral_constant<int, 7>{}); break;
         default: if constexpr (!F3 && sizeof(T) == 4) run(std::integral_constant<int, 8>{}); break;
         }
-    } else {
+    } else if constexpr (NT == kNT) {
         hd = reinterpret_cast<T*>(lines + padded_len(yt * m, x_padl(lm, f3, sizeof(T))));
         hrow = nx;
         load_twiddles(twl, lm, f3, tw);
@@ -2093,7 +2097,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
                 // the inverse radix-3 step (decimation in time) on the way out:
                 // sub-line positions k of both half lines give x = k + t 2^lm
                 const int M = 1 << lm;
-                for (int idx = threadIdx.x; idx < (hp << lm); idx += kNT) {
+                for (int idx = threadIdx.x; idx < (hp << lm); idx += NT) {
                     const int rp = idx >> lm, k = idx & (M - 1);
                     if (k >= nx) continue;
                     const int ie = (2 * rp) * m + k, io = ie + m;
@@ -2118,7 +2122,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
                     }
                 }
             } else {
-                for (int idx = threadIdx.x; idx < hp * m; idx += kNT) {
+                for (int idx = threadIdx.x; idx < hp * m; idx += NT) {
                     const int rp = idx >> lm, x = idx & (m - 1);
                     if (x >= nx) continue;
                     const int ie = (2 * rp) * m + x, io = ie + m;
@@ -2147,11 +2151,11 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     const unsigned zb = (unsigned)z * plb;
     auto at = [&](unsigned o) -> T { return *reinterpret_cast<const T*>(sb + o); };
     int nxp = 1;
-    while (nxp < nx && nxp < kNT) nxp <<= 1;
+    while (nxp < nx && nxp < NT) nxp <<= 1;
     // row groups of nxp lanes: the power of two >= nx, or nx itself where
     // that gives each thread fewer rows (lanes past the last group idle)
-    if (nx < nxp && (yt + kNT / nx - 1) / (kNT / nx) < (yt + kNT / nxp - 1) / (kNT / nxp)) nxp = nx;
-    const int rgs = kNT / nxp;                    // row groups
+    if (nx < nxp && (yt + NT / nx - 1) / (NT / nx) < (yt + NT / nxp - 1) / (NT / nxp)) nxp = nx;
+    const int rgs = NT / nxp;                    // row groups
     const int rg = threadIdx.x / nxp, xl = threadIdx.x - rg * nxp;
     const int rper = (yt + rgs - 1) / rgs;
     const int ra = rg * rper, rb = min(yt, ra + rper);
@@ -2286,7 +2290,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     __syncthreads();
     if ((int)threadIdx.x < nterm) {
         double v = 0;
-        for (int wv = 0; wv < kNT / 64; ++wv) v += red[wv][threadIdx.x];
+        for (int wv = 0; wv < NT / 64; ++wv) v += red[wv][threadIdx.x];
         epart[p.ep_off + ((long long)img * p.tiles + (z * p.nty + ty)) * kNTerm + threadIdx.x] = v;
     }
 }
@@ -3271,12 +3275,16 @@ hipError_t launch_xinv(const Prob* P, int np, const WorkMap* wm, const void* Xp,
                        T* s_star, T* h, double* epart, const void* tw, const int* done, int mode,
                        double tau, double fcp, double fcd, hipStream_t st)
 {
-    if (wm[0].total)
-        hipLaunchKernelGGL((k_xinv<T, 0>), dim3(wm[0].total), dim3(kNT), wm[0].lds, st, P, np, wm[0].start,
-                           (const cplx<T>*)Xp, s, s_star, h, epart, (const cplx<T>*)tw, done, mode, tau, fcp, fcd);
-    if (wm[1].total)
-        hipLaunchKernelGGL((k_xinv<T, 1>), dim3(wm[1].total), dim3(kNT), wm[1].lds, st, P, np, wm[1].start,
-                           (const cplx<T>*)Xp, s, s_star, h, epart, (const cplx<T>*)tw, done, mode, tau, fcp, fcd);
+    auto launch = [&](auto f3, auto nt, const WorkMap& w) {
+        if (w.total)
+            hipLaunchKernelGGL((k_xinv<T, decltype(f3)::value, decltype(nt)::value>), dim3(w.total),
+                               dim3(decltype(nt)::value), w.lds, st, P, np, w.start, (const cplx<T>*)Xp, s, s_star, h,
+                               epart, (const cplx<T>*)tw, done, mode, tau, fcp, fcd);
+    };
+    using std::integral_constant;
+    launch(integral_constant<int, 0>{}, integral_constant<int, kNT>{}, wm[0]);
+    launch(integral_constant<int, 1>{}, integral_constant<int, kNT>{}, wm[1]);
+    launch(integral_constant<int, 0>{}, integral_constant<int, kXinvWide>{}, wm[2]);
     return hipGetLastError();
 }
 

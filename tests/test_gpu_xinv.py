@@ -37,3 +37,27 @@ def test_inverse_x_lengths_and_tiles_vs_oracle(oracle, tmp_path, precision, nx, 
         cache.write_text(f"{dev} {precision} {nx}x{ny}x{nz} 2 8 {rows} 1\n")
         sm.autotune(str(cache))
         assert torch.equal(sm.eval(s)[1], h), rows
+
+
+@pytest.mark.parametrize("precision", [ssm.SSM_FP64, ssm.SSM_FP32_MIXED])
+@pytest.mark.parametrize("nx,ny,nz", [(1, 3, 1), (31, 33, 1), (33, 64, 2), (63, 31, 3), (64, 65, 1)])
+def test_wide_workgroups(oracle, precision, nx, ny, nz):
+    """The shortest power-of-two lengths (workgroups of kXinvWide threads):
+    field and energy against the oracle, and bitwise the same in a batch with
+    problems of the other kinds."""
+    p = dict(nx=nx, ny=ny, nz=nz, K=3, J=0.9, d=0.35, ku=0.21, D=0.4)
+    s = inputs.random_unit_spins((3, 3, nz, ny, nx), seed=nx + ny)
+    if precision == ssm.SSM_FP32_MIXED:
+        s = s.astype(np.float32).astype(np.float64)
+    E, h = ssm.StringMethod(p, precision).eval(s)[:2]
+    for k in range(3):
+        ho = oracle.field(s[k], p["J"], p["d"], p["ku"], p["D"])
+        assert np.abs(h[k].cpu().numpy() - ho).max() < TOL[precision] * np.abs(ho).max(), k
+        scale = 0.5 * np.abs(s[k] * ho).sum()
+        assert abs(E[k].item() + 0.5 * (s[k] * ho).sum()) < TOL[precision] * scale, k
+    others = [dict(p, nx=45, K=2), dict(p, nx=100, K=2)]
+    so = [inputs.random_unit_spins((2, 3, nz, ny, q["nx"]), seed=5) for q in others]
+    batch = ssm.StringMethod([others[0], p, others[1]], precision)
+    Eb, hb = batch.eval(np.concatenate([so[0].ravel(), s.ravel(), so[1].ravel()]))[:2]
+    assert torch.equal(Eb[2:5], E)
+    assert torch.equal(hb.reshape(-1)[so[0].size:so[0].size + s.size], h.reshape(-1))
