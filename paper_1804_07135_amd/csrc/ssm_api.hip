@@ -679,6 +679,14 @@ struct Ops {
             return launch_arc<T>(c->P(), pl.np, c->wm_arc(), ss, c->at<double>(pl.o_ap), done, st);
         });
         if (e != hipSuccess) return e;
+        if (pl.red_kinds == 2 && o.opts == 0)
+            return timed(c, st, KK_INTERP, [&] {
+                return launch_interp1<T>(c->P(), pl.np, c->wm_site4(), ss, s, done, c->at<double>(pl.o_ep),
+                                         c->at<double>(pl.o_ap), write_E ? c->at<double>(pl.o_E) : nullptr,
+                                         c->at<double>(pl.o_seg), c->at<double>(pl.o_alpha), c->at<int>(pl.o_j),
+                                         c->at<double>(pl.o_w), c->at<int>(pl.o_skip), c->at<int>(pl.o_iters),
+                                         flags, st, o);
+            });
         e = timed(c, st, KK_REDUCE, [&] {
             return launch_reduce(c->P(), pl.np, (int)pl.n_img, pl.red_kinds, c->wm_img().start,
                                  c->at<double>(pl.o_ep), c->at<double>(pl.o_ap),

@@ -345,6 +345,12 @@ hipError_t launch_reduce(const Prob* P, int np, int nimg, int kinds, const int* 
                          double* seg, double* alpha, int* jidx, double* wgt, int* skip, int* done,
                          int* iters, int* count, int* flags, int with_arc, hipStream_t st,
                          Step2 s2 = Step2{});
+// launch_reduce (with_arc, no options) and launch_interp in one, for batches of
+// red1 problems only
+template <typename T>
+hipError_t launch_interp1(const Prob* P, int np, const WorkMap& wm, const T* ss, T* s, const int* done,
+                          const double* epart, const double* apart, double* E, double* seg, double* alpha,
+                          int* jidx, double* wgt, int* skip, int* iters, int* flags, hipStream_t st, Step2 s2);
 template <typename T>
 // kci (or NULL): per-problem climbing image, copied like the endpoints;
 // skip_if (or NULL): problems whose flag is set are left to the spline

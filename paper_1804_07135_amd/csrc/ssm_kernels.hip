@@ -2359,21 +2359,12 @@ __global__ __launch_bounds__(kNT) void k_arc(const Prob* __restrict__ P, int np,
     }
 }
 
-// ---------------------------------------------------------------------------
-// The end of step 2 for problem pi, by one workgroup.  al[0..K) (LDS) holds
-// the segment lengths |phi*_k - phi*_{k-1}| (al[0] = 0); el is LDS for K
-// energies.  Scans them in a fixed order into S_k, alpha*_k = S_k/S_{K-1}
-// and, for every interior image, the interval
-// j = max{j <= K-2 : alpha*_j <= target} and its weight; with the options,
-// the climbing image and the spline factors.
-// ---------------------------------------------------------------------------
-__device__ void reduce_final(const Prob& p, int pi, double* al, double* el, double* bc, int* s_kci,
-                             double* alpha, int* jidx, double* wgt, int* skip, int* iters, const Step2& s2)
+// al[0..K) (LDS): segment lengths (al[0] = 0) -> S_k = al[1] + ... + al[k], the
+// total to *bc: an inclusive scan by the first wavefront, 64 images at a time
+// with the running total carried over (a fixed order, so reruns are bitwise
+// identical).
+__device__ void reduce_scan(int K, double* al, double* bc)
 {
-    const int K = p.K, g0 = p.img0;
-    // S_k = al[1] + ... + al[k]: an inclusive scan by the first wavefront,
-    // 64 images at a time with the running total carried over (a fixed
-    // order, so reruns are bitwise identical)
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         double carry = 0.0;
@@ -2390,13 +2381,51 @@ __device__ void reduce_final(const Prob& p, int pi, double* al, double* el, doub
             if (in) al[kk] = v;
             carry = __shfl(v, 63);
         }
-        if (lane == 0) {
-            *bc = carry;
-            skip[pi] = (carry > 0.0) ? 0 : 1;
-            atomicAdd(&iters[pi], 1);  // the problem's only writer in this launch
-        }
+        if (lane == 0) *bc = carry;
     }
     __syncthreads();
+}
+
+// Interval of target t >= 0: the largest j <= K-2 with al[j] <= t, by
+// bisection (al is non-decreasing from al[0] = 0; with non-finite lengths j
+// still lies in 0..K-2).
+__device__ __forceinline__ int reduce_interval(const double* al, int K, double t)
+{
+    int lo = 0, hi = K - 2;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (al[mid] <= t) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// The weight of target t in its interval j.
+__device__ __forceinline__ double reduce_weight(const double* al, int j, double t)
+{
+    const double width = al[j + 1] - al[j];
+    return (width > 0.0) ? (t - al[j]) / width : 0.0;
+}
+
+// ---------------------------------------------------------------------------
+// The end of step 2 for problem pi, by one workgroup.  al[0..K) (LDS) holds
+// the segment lengths |phi*_k - phi*_{k-1}| (al[0] = 0); el is LDS for K
+// energies.  Scans them in a fixed order into S_k, alpha*_k = S_k/S_{K-1}
+// and, for every interior image, the interval
+// j = max{j <= K-2 : alpha*_j <= target} and its weight; with the options
+// (none without OPTS), the climbing image and the spline factors.
+// ---------------------------------------------------------------------------
+template <bool OPTS = true>
+__device__ void reduce_final(const Prob& p, int pi, double* al, double* el, double* bc, int* s_kci,
+                             double* alpha, int* jidx, double* wgt, int* skip, int* iters, const Step2& s2)
+{
+    const int K = p.K, g0 = p.img0;
+    const int opts = OPTS ? s2.opts : 0;
+    reduce_scan(K, al, bc);
+    if (threadIdx.x == 0) {
+        skip[pi] = (*bc > 0.0) ? 0 : 1;
+        atomicAdd(&iters[pi], 1);  // the problem's only writer in this launch
+    }
     const double L = *bc;
     if (!(L > 0.0)) {
         for (int kk = threadIdx.x; kk < K; kk += kNT) {
@@ -2411,7 +2440,7 @@ __device__ void reduce_final(const Prob& p, int pi, double* al, double* el, doub
         return;
     }
     for (int kk = 1 + threadIdx.x; kk < K; kk += kNT) al[kk] = al[kk] / L;
-    if (s2.opts & 2) {
+    if (opts & 2) {
         const volatile double* Ev = s2.E;
         for (int kk = threadIdx.x; kk < K; kk += kNT) el[kk] = Ev[g0 + kk];
     }
@@ -2420,7 +2449,7 @@ __device__ void reduce_final(const Prob& p, int pi, double* al, double* el, doub
         // climbing image: the image of highest energy (smallest index on
         // ties) when it is interior
         int kci = -1;
-        if (s2.opts & 2) {
+        if (opts & 2) {
             int km = 0;
             double em = el[0];
             for (int kk = 1; kk < K; ++kk) {
@@ -2441,18 +2470,6 @@ __device__ void reduce_final(const Prob& p, int pi, double* al, double* el, doub
         if (kk <= kci) return al[kci] * (double)kk / (double)kci;
         return al[kci] + (1.0 - al[kci]) * (double)(kk - kci) / (double)(K - 1 - kci);
     };
-    // interval of target t >= 0: the largest j <= K-2 with al[j] <= t, by
-    // bisection (al is non-decreasing from al[0] = 0; with non-finite
-    // lengths j still lies in 0..K-2)
-    auto interval = [&](double t) {
-        int lo = 0, hi = K - 2;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (al[mid] <= t) lo = mid;
-            else hi = mid - 1;
-        }
-        return lo;
-    };
     for (int kk = threadIdx.x; kk < K; kk += kNT) {
         alpha[g0 + kk] = al[kk];
         if (kk == 0 || kk == K - 1 || kk == kci) {
@@ -2461,12 +2478,11 @@ __device__ void reduce_final(const Prob& p, int pi, double* al, double* el, doub
             continue;
         }
         const double tk = target(kk);
-        const int j = interval(tk);
-        const double width = al[j + 1] - al[j];
+        const int j = reduce_interval(al, K, tk);
         jidx[g0 + kk] = j;
-        wgt[g0 + kk] = (width > 0.0) ? (tk - al[j]) / width : 0.0;
+        wgt[g0 + kk] = reduce_weight(al, j, tk);
     }
-    if (!(s2.opts & 1)) return;
+    if (!(opts & 1)) return;
     // the one-pass spline step's operator is formed here for K <= wmax
     // (copies of the factors and targets kept in LDS for it)
     const bool wop = K <= s2.wmax;
@@ -2501,7 +2517,7 @@ __device__ void reduce_final(const Prob& p, int pi, double* al, double* el, doub
     for (int kk = threadIdx.x; kk < K; kk += kNT) {
         if (kk == 0 || kk == K - 1 || kk == kci) continue;
         const double tk = target(kk);
-        const int j = interval(tk);
+        const int j = reduce_interval(al, K, tk);
         const double h = al[j + 1] - al[j];
         const double A = (al[j + 1] - tk) / h;
         s2.A[g0 + kk] = A;
@@ -2651,31 +2667,18 @@ __global__ __launch_bounds__(kNT) void k_reduce(const Prob* __restrict__ P, int 
 }
 
 // ---------------------------------------------------------------------------
-// k_reduce1: the whole reduction of one problem with red1 (few images and
-// few partials per image) in one workgroup, so that no result passes
-// between workgroups: the device-scope fences of that hand-off cost more
-// than these sums.  kRedLanes lanes per image sum its partials in rounds,
-// then combine them in a fixed butterfly order (4 lanes: the 64 images of
-// the largest such problem in one pass, so the partials' loads wait on
-// memory once); with_arc, reduce_final ends step 2 from the segment
-// lengths kept in LDS.
+// The sums of a problem with red1 (few images and few partials per image) by
+// one workgroup: kRedLanes lanes per image sum its partials in rounds, then
+// combine them in a fixed butterfly order (4 lanes: the 64 images of the
+// largest such problem in one pass, so the partials' loads wait on memory
+// once).  ENERGY: energies and terms to their places; with_arc: the segment
+// lengths to al (LDS) and, with ENERGY, to seg.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kNT) void k_reduce1(const Prob* __restrict__ P, int np,
-                                                 const double* __restrict__ epart,
-                                                 const double* __restrict__ apart,
-                                                 double* E, double* Tm, double* E_out,
-                                                 double* T_out, double* seg, double* alpha,
-                                                 int* jidx, double* wgt, int* skip, int* done,
-                                                 int* iters, int* flags, int with_arc, Step2 s2)
+template <bool ENERGY>
+__device__ __forceinline__ void reduce1_sums(const Prob& p, const double* __restrict__ epart,
+                                             const double* __restrict__ apart, double* E, double* Tm, double* E_out,
+                                             double* T_out, double* seg, int* flags, int with_arc, double* al)
 {
-    __shared__ double al[kMaxImages], el[kMaxImages];
-    __shared__ double bc;
-    __shared__ int s_kci;
-    const int pi = blockIdx.x;
-    if (pi >= np) return;
-    if (with_arc && done && done[pi]) return;
-    const Prob& p = P[pi];
-    if (!p.red1) return;  // reduced by k_reduce
     const int K = p.K, g0 = p.img0, nt = p.tiles, na = p.arc_chunks * 4;
     constexpr int IPP = kNT / kRedLanes;  // images per pass
     constexpr int RE = 4, RA = 8;
@@ -2684,20 +2687,22 @@ __global__ __launch_bounds__(kNT) void k_reduce1(const Prob* __restrict__ P, int
         const int k = k0 + (int)threadIdx.x / kRedLanes;
         const int kc = min(k, K - 1);  // lanes past the last image repeat it and store nothing
         double v[kNTerm + 1] = {0, 0, 0, 0, 0, 0};
-        const double* ep = epart + p.ep_off + (long long)kc * nt * kNTerm;
-        for (int t0 = sub; t0 < nt; t0 += RE * kRedLanes) {
-            double q[RE][kNTerm];
+        if constexpr (ENERGY) {
+            const double* ep = epart + p.ep_off + (long long)kc * nt * kNTerm;
+            for (int t0 = sub; t0 < nt; t0 += RE * kRedLanes) {
+                double q[RE][kNTerm];
 #pragma unroll
-            for (int u = 0; u < RE; ++u) {
-                const long long t = min(t0 + u * kRedLanes, nt - 1);
+                for (int u = 0; u < RE; ++u) {
+                    const long long t = min(t0 + u * kRedLanes, nt - 1);
 #pragma unroll
-                for (int j = 0; j < kNTerm; ++j) q[u][j] = ep[t * kNTerm + j];
+                    for (int j = 0; j < kNTerm; ++j) q[u][j] = ep[t * kNTerm + j];
+                }
+#pragma unroll
+                for (int u = 0; u < RE; ++u)
+                    if (t0 + u * kRedLanes < nt)
+#pragma unroll
+                        for (int j = 0; j < kNTerm; ++j) v[j] += q[u][j];
             }
-#pragma unroll
-            for (int u = 0; u < RE; ++u)
-                if (t0 + u * kRedLanes < nt)
-#pragma unroll
-                    for (int j = 0; j < kNTerm; ++j) v[j] += q[u][j];
         }
         if (with_arc && kc > 0) {
             const double* ap = apart + p.ap_off + (long long)kc * na;
@@ -2713,23 +2718,50 @@ __global__ __launch_bounds__(kNT) void k_reduce1(const Prob* __restrict__ P, int
 #pragma unroll
         for (int off = kRedLanes / 2; off > 0; off >>= 1)
 #pragma unroll
-            for (int j = 0; j <= kNTerm; ++j) v[j] += __shfl_xor(v[j], off, kRedLanes);
+            for (int j = ENERGY ? 0 : kNTerm; j <= kNTerm; ++j) v[j] += __shfl_xor(v[j], off, kRedLanes);
         if (sub == 0 && k < K) {
             const int g = g0 + k;
-            if (E) E[g] = v[0];
-            if (E_out) E_out[g] = v[0];
-            for (int j = 0; j < 4; ++j) {
-                if (Tm) Tm[(long long)g * 4 + j] = v[j + 1];
-                if (T_out) T_out[(long long)g * 4 + j] = v[j + 1];
+            if constexpr (ENERGY) {
+                if (E) E[g] = v[0];
+                if (E_out) E_out[g] = v[0];
+                for (int j = 0; j < 4; ++j) {
+                    if (Tm) Tm[(long long)g * 4 + j] = v[j + 1];
+                    if (T_out) T_out[(long long)g * 4 + j] = v[j + 1];
+                }
+                if (!isfinite(v[0])) atomicOr(flags, 1);
             }
-            if (!isfinite(v[0])) atomicOr(flags, 1);
             if (with_arc) {
                 const double sl = sqrt(v[kNTerm]);
-                seg[g] = sl;
+                if constexpr (ENERGY) seg[g] = sl;
                 al[k] = (k == 0) ? 0.0 : sl;
             }
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// k_reduce1: the whole reduction of one problem with red1 in one workgroup, so
+// that no result passes between workgroups: the device-scope fences of that
+// hand-off cost more than these sums.  With_arc, reduce_final ends step 2 from
+// the segment lengths kept in LDS.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kNT) void k_reduce1(const Prob* __restrict__ P, int np,
+                                                 const double* __restrict__ epart,
+                                                 const double* __restrict__ apart,
+                                                 double* E, double* Tm, double* E_out,
+                                                 double* T_out, double* seg, double* alpha,
+                                                 int* jidx, double* wgt, int* skip, int* done,
+                                                 int* iters, int* flags, int with_arc, Step2 s2)
+{
+    __shared__ double al[kRed1MaxK], el[kRed1MaxK];
+    __shared__ double bc;
+    __shared__ int s_kci;
+    const int pi = blockIdx.x;
+    if (pi >= np) return;
+    if (with_arc && done && done[pi]) return;
+    const Prob& p = P[pi];
+    if (!p.red1) return;  // reduced by k_reduce
+    reduce1_sums<true>(p, epart, apart, E, Tm, E_out, T_out, seg, flags, with_arc, al);
     if (!with_arc) return;
     __syncthreads();
     reduce_final(p, pi, al, el, &bc, &s_kci, alpha, jidx, wgt, skip, iters, s2);
@@ -2760,33 +2792,15 @@ __device__ __forceinline__ void interp_site(const T (&a)[3], const T (&b)[3], do
     }
 }
 
-// ---------------------------------------------------------------------------
-// k_interp: s_k = normalise((1-w) s*_j + w s*_{j+1}); endpoints (and every
-// image when the reparametrisation is skipped) are copied.
-// ---------------------------------------------------------------------------
+// The sites of workgroup item (image k, chunk) of problem p: a copy, or the
+// interpolation from images j and j + 1 with weight wt.
 template <typename T>
-__global__ __launch_bounds__(kNT) void k_interp(const Prob* __restrict__ P, int np,
-                                                const int* __restrict__ wstart,
-                                                const T* __restrict__ ss, T* __restrict__ s,
-                                                const int* __restrict__ jidx,
-                                                const double* __restrict__ wgt,
-                                                const int* __restrict__ skip,
-                                                const int* __restrict__ done, int* flags,
-                                                const int* __restrict__ kci,
-                                                const int* __restrict__ skip_if)
+__device__ __forceinline__ void interp_chunk(const Prob& p, int k, int chunk, const T* __restrict__ ss,
+                                             T* __restrict__ s, bool copy, int j, double wt, int* flags)
 {
-    const int pi = find_problem(wstart, np, blockIdx.x);
-    int w0;
-    bool off;
-    const Prob& p = problem(P, pi, wstart, done, w0, off);
-    if (off) return;
-    if (skip_if && skip_if[pi]) return;
-    const int w = blockIdx.x - w0;
-    const int k = w / p.ichunks4, chunk = w - k * p.ichunks4;
     const long long N = p.N, M = 3 * N;
     const T* src = ss + p.s_off;
     T* dst = s + p.s_off + (long long)k * M;
-    const bool copy = skip[pi] || k == 0 || k == p.K - 1 || (kci && k == kci[pi]);
     if constexpr (sizeof(T) == 4) {
         if (p.vec4) {
             // four consecutive sites per thread, 16-byte accesses
@@ -2799,8 +2813,6 @@ __global__ __launch_bounds__(kNT) void k_interp(const Prob* __restrict__ P, int 
                         *reinterpret_cast<const float4*>(src + (long long)k * M + c * N + i);
                 return;
             }
-            const int j = jidx[p.img0 + k];
-            const double wt = wgt[p.img0 + k];
             const T* a = src + (long long)j * M;
             const T* b = a + M;
             float av[3][4], bv[3][4];
@@ -2836,8 +2848,6 @@ __global__ __launch_bounds__(kNT) void k_interp(const Prob* __restrict__ P, int 
                         *reinterpret_cast<const double2*>(src + (long long)k * M + c * N + i);
                 return;
             }
-            const int j = jidx[p.img0 + k];
-            const double wt = wgt[p.img0 + k];
             const T* a = src + (long long)j * M;
             const T* b = a + M;
             double av[3][2], bv[3][2];
@@ -2869,8 +2879,6 @@ __global__ __launch_bounds__(kNT) void k_interp(const Prob* __restrict__ P, int 
         for (int c = 0; c < 3; ++c) dst[c * N + i] = src[(long long)k * M + c * N + i];
         return;
     }
-    const int j = jidx[p.img0 + k];
-    const double wt = wgt[p.img0 + k];
     const T* a = src + (long long)j * M;
     const T* b = a + M;
     T ta[3], tb[3], to[3];
@@ -2882,6 +2890,90 @@ __global__ __launch_bounds__(kNT) void k_interp(const Prob* __restrict__ P, int 
     interp_site<T>(ta, tb, wt, to, flags);
 #pragma unroll
     for (int c = 0; c < 3; ++c) dst[c * N + i] = to[c];
+}
+
+// ---------------------------------------------------------------------------
+// k_interp: s_k = normalise((1-w) s*_j + w s*_{j+1}); endpoints (and every
+// image when the reparametrisation is skipped) are copied.
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(kNT) void k_interp(const Prob* __restrict__ P, int np,
+                                                const int* __restrict__ wstart,
+                                                const T* __restrict__ ss, T* __restrict__ s,
+                                                const int* __restrict__ jidx,
+                                                const double* __restrict__ wgt,
+                                                const int* __restrict__ skip,
+                                                const int* __restrict__ done, int* flags,
+                                                const int* __restrict__ kci,
+                                                const int* __restrict__ skip_if)
+{
+    const int pi = find_problem(wstart, np, blockIdx.x);
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
+    if (skip_if && skip_if[pi]) return;
+    const int w = blockIdx.x - w0;
+    const int k = w / p.ichunks4, chunk = w - k * p.ichunks4;
+    const bool copy = skip[pi] || k == 0 || k == p.K - 1 || (kci && k == kci[pi]);
+    interp_chunk<T>(p, k, chunk, ss, s, copy, jidx[p.img0 + k], wgt[p.img0 + k], flags);
+}
+
+// ---------------------------------------------------------------------------
+// k_interp1: k_reduce1 (with_arc, no options) and k_interp in one launch,
+// where every problem has red1: a launch of its own costs the reduction more
+// than each interpolating workgroup's sum of the few arc partials (read from
+// L2) and scan of at most 64 lengths.  Every workgroup does the same
+// operations in the same order, so all have the same lengths; the problem's
+// first one also does the rest of the reduction (energies, outputs).  Bound by
+// latency.  Us an iteration, two launches -> one: FP64 32 x 32, 10 images 28.0
+// -> 25.3; FP32 64 x 64, 20 images 36.0 -> 32.9 and 64 images 52.6 -> 44.6; 112 x
+// 112, 60 images 69.8 -> 65.4, four of them 163.7 -> 160.8; 64 problems of 96 x 96,
+// 16 images 430.6 -> 427.7.  The largest red1 problems (128 x 128, 64 images, FP64)
+// come out even.
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(kNT) void k_interp1(const Prob* __restrict__ P, int np, const int* __restrict__ wstart,
+                                                 const T* __restrict__ ss, T* __restrict__ s,
+                                                 const int* __restrict__ done, const double* __restrict__ epart,
+                                                 const double* __restrict__ apart, double* E, double* seg,
+                                                 double* alpha, int* jidx, double* wgt, int* skip, int* iters,
+                                                 int* flags, Step2 s2)
+{
+    __shared__ double al[kRed1MaxK];
+    __shared__ double bc;
+    __shared__ int s_kci;
+    const int pi = find_problem(wstart, np, blockIdx.x);
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
+    const int w = blockIdx.x - w0, K = p.K;
+    const int k = w / p.ichunks4, chunk = w - k * p.ichunks4;
+    if (w == 0) {
+        reduce1_sums<true>(p, epart, apart, E, nullptr, nullptr, nullptr, seg, flags, 1, al);
+        __syncthreads();
+        reduce_final<false>(p, pi, al, nullptr, &bc, &s_kci, alpha, jidx, wgt, skip, iters, s2);
+        __syncthreads();
+    } else {
+        reduce1_sums<false>(p, epart, apart, nullptr, nullptr, nullptr, nullptr, nullptr, flags, 1, al);
+        __syncthreads();
+        reduce_scan(K, al, &bc);
+        if (bc > 0.0) {
+            const double L = bc;
+            for (int kk = 1 + threadIdx.x; kk < K; kk += kNT) al[kk] = al[kk] / L;
+        }
+        __syncthreads();
+    }
+    const bool copy = !(bc > 0.0) || k == 0 || k == K - 1;
+    int j = 0;
+    double wt = 0.0;
+    if (!copy) {
+        const double tk = (double)k / (double)(K - 1);
+        j = reduce_interval(al, K, tk);
+        wt = reduce_weight(al, j, tk);
+    }
+    interp_chunk<T>(p, k, chunk, ss, s, copy, j, wt, flags);
 }
 
 // ---------------------------------------------------------------------------
@@ -3319,6 +3411,17 @@ hipError_t launch_interp(const Prob* P, int np, const WorkMap& wm, const T* ss, 
     if (wm.total == 0) return hipSuccess;
     hipLaunchKernelGGL(k_interp<T>, dim3(wm.total), dim3(kNT), 0, st, P, np, wm.start, ss, s, jidx,
                        wgt, skip, done, flags, kci, skip_if);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_interp1(const Prob* P, int np, const WorkMap& wm, const T* ss, T* s, const int* done,
+                          const double* epart, const double* apart, double* E, double* seg, double* alpha,
+                          int* jidx, double* wgt, int* skip, int* iters, int* flags, hipStream_t st, Step2 s2)
+{
+    if (wm.total == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_interp1<T>, dim3(wm.total), dim3(kNT), 0, st, P, np, wm.start, ss, s, done, epart, apart, E,
+                       seg, alpha, jidx, wgt, skip, iters, flags, s2);
     return hipGetLastError();
 }
 
@@ -4098,6 +4201,9 @@ hipError_t launch_fill_double(double* p, int n, double v, hipStream_t st)
                                        double, double, hipStream_t);                               \
     template hipError_t launch_arc<T>(const Prob*, int, const WorkMap&, const T*, double*,        \
                                       const int*, hipStream_t);                                    \
+    template hipError_t launch_interp1<T>(const Prob*, int, const WorkMap&, const T*, T*, const int*, \
+                                          const double*, const double*, double*, double*, double*, int*, double*, \
+                                          int*, int*, int*, hipStream_t, Step2);                  \
     template hipError_t launch_interp<T>(const Prob*, int, const WorkMap&, const T*, T*,          \
                                          const int*, const double*, const int*, const int*, int*, \
                                          hipStream_t, const int*, const int*);                     \
