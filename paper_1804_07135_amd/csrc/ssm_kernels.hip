@@ -6,7 +6,11 @@
 //            components (Sec. II.A: the dipolar field of eq. (6) is a
 //            circular convolution once the lattice is padded);
 //   k_conv   for each x-frequency: FFTs along y (and z), multiplication by
-//            the FFT of the point-dipole tensor of eq. (7), inverse FFTs;
+//            the FFT of the point-dipole tensor of eq. (7), inverse FFTs
+//            (k_conv1 for monolayers and k_convz for several layers, in
+//            place, where a slice fits in LDS with both halves of its padded
+//            y transform; k_convh and k_conv, one half after the other, where
+//            it doesn't);
 //   k_xinv   inverse FFT along x, then per site: exchange, DMI and
 //            anisotropy stencils (eqs. (3)-(5)), the energy -1/2 h.s of
 //            eq. (8) reduced in FP64, and the projected descent step with
@@ -16,7 +20,8 @@
 //            interpolation interval/weight of every image (one workgroup
 //            per image, or k_reduce1: one per small problem);
 //   k_interp linear interpolation onto alpha_k = k/(K-1) + renormalisation
-//            (or the spline step of the options).
+//            (or the spline step of the options); k_interp1 does both last
+//            steps where every problem is small.
 //
 // Padded lengths are P = 2m with m >= n a power of two, or 3 2^a where that
 // is smaller.  A zero-padded length-P transform of n <= m inputs is two
@@ -30,7 +35,8 @@
 // Length-m transforms run in LDS as Stockham passes (radix 16 first at the
 // compile-time lengths, radix 4 and 2 otherwise; a radix-3 step for 3 2^a);
 // every line belongs to one wavefront, which needs no workgroup barrier
-// between passes.
+// between passes (or, in the in-place convolutions and xinv_two_step, every
+// thread takes an item of a pass and barriers lie between the passes).
 #include "ssm_fft.hpp"
 #include "ssm_internal.hpp"
 
@@ -511,10 +517,10 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 // result goes to the output slice and the y half 1 result is added onto it
 // (each thread adds onto the values it stored itself).  The kernel
 // spectrum carries 1/(Px Py Pz).
+// Serves what the kernels below don't: 5 to 8 layers at the y lengths k_convz
+// can't hold, 9 to 16 layers, and y lengths without a compile-time build.
 // LDS: twiddles (2 m_y) + G*3*nz lines of m_y.
 // ---------------------------------------------------------------------------
-
-
 
 // multiply by the padded-z twiddle exp(-2 pi i zz / (2 MZ)) (conjugate for
 // INV); zz is a compile-time constant after unrolling
