@@ -703,11 +703,14 @@ struct Ops {
         const int kw = SSM_SPLW ? (kSplwMax<T> >= 32 ? pl.kmax_le32 : pl.kmax_le16) : 0;
         const int kskip = SSM_SPLW ? kSplwMax<T> : 0;
         if ((o.opts & 1) && kw > 0) {
+            // every problem in the one pass: its degenerate splines too
+            const bool all = pl.kmax <= kskip;
             e = timed(c, st, KK_INTERP, [&] {
                 return launch_interp_splw<T>(c->P(), pl.np, c->wm_sitep(), kw, ss, s, c->at<int>(pl.o_j),
-                                             c->at<double>(pl.o_w), o, done, flags, st);
+                                             c->at<double>(pl.o_w), o, done, flags,
+                                             all ? c->at<int>(pl.o_skip) : nullptr, st);
             });
-            if (e != hipSuccess) return e;
+            if (e != hipSuccess || all) return e;
         }
         if ((o.opts & 1) && pl.kmax > kskip) {
             T* M = c->at<T>(pl.o_h);

@@ -372,13 +372,15 @@ hipError_t launch_interp_spline(const Prob* P, int np, const WorkMap& wm, const 
 // (one thread per site, wm_sitep); kmax: the largest of their image
 // counts; problems with more images are left to the two kernels above, so
 // each problem takes the same path whatever else is in the batch
+// (lin, or NULL: the skip flags; a problem with a degenerate spline then takes
+// the linear step there as well, the same bits as launch_interp's)
 template <typename T>
 constexpr int kSplwMax = sizeof(T) == 4 ? 32 : 16;
 static_assert(kSplwMax<float> <= kWRow && kSplwMax<double> <= kWRow, "operator rows");
 template <typename T>
 hipError_t launch_interp_splw(const Prob* P, int np, const WorkMap& wm_sitep, int kmax, const T* ss, T* s,
                               const int* jidx, const double* wgt, Step2 s2, const int* done, int* flags,
-                              hipStream_t st);
+                              const int* lin, hipStream_t st);
 // climbing image: partial sums (|t~|^2, F.t~) over image kci, their
 // per-problem reduction to c = F.t~ / |t~|^2, and the step
 // normalise(s + tau (F - 2 c t~)) into ss

@@ -3890,20 +3890,47 @@ __global__ __launch_bounds__(kNT) void k_interp_spline(const Prob* __restrict__ 
 // then the spline formula of k_interp_spline) is formed once by the end of
 // step 2 (reduce_final); each workgroup loads it into LDS, and each thread
 // then reads its site's K images once and writes the K targets.  Endpoints
-// and the climbing image are copied.
+// and the climbing image are copied.  With lin (skip flags), the problems
+// whose spline is degenerate take the linear step here too, so that batches
+// of such problems alone need no launch of k_interp, which otherwise comes
+// after (64 problems of 48..96 sites, 16 images: 7 us of an iteration).
 template <typename T, int KMAX>
 __global__ __launch_bounds__(kNT) void k_interp_splw(const Prob* __restrict__ P, int np,
                                                      const int* __restrict__ wstart, const T* __restrict__ ss,
                                                      T* __restrict__ s, const int* __restrict__ jidx,
                                                      const double* __restrict__ wgt, Step2 s2,
-                                                     const int* __restrict__ done, int* flags)
+                                                     const int* __restrict__ done, int* flags,
+                                                     const int* __restrict__ lin)
 {
     __shared__ double W[KMAX][KMAX];
     const int pi = find_problem(wstart, np, blockIdx.x);
-    if ((done && done[pi]) || !s2.spl_ok[pi]) return;
+    if (done && done[pi]) return;
+    const bool ok = s2.spl_ok[pi];
+    if (!ok && !lin) return;
     const Prob& p = P[pi];
     if (p.K > KMAX) return;  // served by k_spline_m and k_interp_spline
     const int K = p.K, g0 = p.img0, kci = s2.kci ? s2.kci[pi] : -1;
+    if (!ok) {
+        const long long N = p.N, Ms = 3 * N, i = (long long)(blockIdx.x - wstart[pi]) * kNT + threadIdx.x;
+        if (i >= N) return;
+        const T* src = ss + p.s_off + i;
+        T* dst = s + p.s_off + i;
+        for (int k = 0; k < K; ++k) {
+            const bool copy = lin[pi] || k == 0 || k == K - 1 || k == kci;
+            const T* a = src + (long long)(copy ? k : jidx[g0 + k]) * Ms;
+            T ta[3], tb[3], to[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                ta[c] = a[c * N];
+                tb[c] = copy ? ta[c] : a[Ms + c * N];
+                to[c] = ta[c];
+            }
+            if (!copy) interp_site<T>(ta, tb, wgt[g0 + k], to, flags);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) dst[k * Ms + c * N] = to[c];
+        }
+        return;
+    }
     // the problem's operator, formed by the end of step 2
     for (int e = threadIdx.x; e < KMAX * KMAX; e += kNT) {
         const int k = e / KMAX, i = e % KMAX;
@@ -4128,16 +4155,16 @@ hipError_t launch_interp_spline(const Prob* P, int np, const WorkMap& wm, const 
 template <typename T>
 hipError_t launch_interp_splw(const Prob* P, int np, const WorkMap& wm_sitep, int kmax, const T* ss, T* s,
                               const int* jidx, const double* wgt, Step2 s2, const int* done, int* flags,
-                              hipStream_t st)
+                              const int* lin, hipStream_t st)
 {
     if (wm_sitep.total == 0) return hipSuccess;
     if (kmax > kSplwMax<T>) return hipErrorInvalidValue;
     if (kmax <= 16) {
         hipLaunchKernelGGL((k_interp_splw<T, 16>), dim3(wm_sitep.total), dim3(kNT), 0, st, P, np, wm_sitep.start,
-                           ss, s, jidx, wgt, s2, done, flags);
+                           ss, s, jidx, wgt, s2, done, flags, lin);
     } else if constexpr (kSplwMax<T> >= 32) {
         hipLaunchKernelGGL((k_interp_splw<T, 32>), dim3(wm_sitep.total), dim3(kNT), 0, st, P, np, wm_sitep.start,
-                           ss, s, jidx, wgt, s2, done, flags);
+                           ss, s, jidx, wgt, s2, done, flags, lin);
     }
     return hipGetLastError();
 }
@@ -4217,7 +4244,7 @@ hipError_t launch_fill_double(double* p, int n, double v, hipStream_t st)
                                            const int*, int, hipStream_t);                          \
     template hipError_t launch_interp_splw<T>(const Prob*, int, const WorkMap&, int, const T*, T*, \
                                               const int*, const double*, Step2, const int*, int*,  \
-                                              hipStream_t);                                        \
+                                              const int*, hipStream_t);                            \
     template hipError_t launch_interp_spline<T>(const Prob*, int, const WorkMap&, const T*,        \
                                                 const T*, T*, const int*, const double*, Step2,    \
                                                 const int*, int*, int, hipStream_t);               \

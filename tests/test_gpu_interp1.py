@@ -32,3 +32,30 @@ def test_same_as_two_launches(precision, nx, ny, nz, K, still):
     assert torch.equal(a[:n], b[:n]) and torch.equal(a[n:], b[n + sl.size:])
     e, f = one.energies(), two.energies()
     assert torch.equal(e[:K], f[:K]) and torch.equal(e[K:], f[K + 65:])
+
+
+@pytest.mark.parametrize("precision", [ssm.SSM_FP64, ssm.SSM_FP32_MIXED])
+@pytest.mark.parametrize("climb", [False, True])
+@pytest.mark.parametrize("kind", ["spline", "two", "repeat", "still"])
+def test_spline_pass_takes_degenerate_splines(precision, climb, kind):
+    """The one-pass spline step of problems with few images (k_interp_splw)
+    takes a degenerate spline's linear step too: bitwise what k_interp gives
+    such a problem in a batch with one of more images (two images, two equal
+    neighbours, no arc length at all)."""
+    K = 2 if kind == "two" else 6
+    p = dict(nx=9, ny=7, nz=1, K=K, J=0.9, d=0.35, ku=0.21, D=0.02)
+    s = inputs.random_unit_spins((K, 3, 1, 7, 9), seed=3)
+    if kind == "repeat":
+        s[3] = s[2]
+    if kind == "still":
+        s[:] = s[:1]
+    long = dict(p, nx=3, ny=2, K=40)
+    sl = inputs.random_unit_spins((40, 3, 1, 2, 3), seed=1)
+    one, two = ssm.StringMethod(p, precision), ssm.StringMethod([p, long], precision)
+    out = []
+    for sm, x in ((one, s.ravel()), (two, np.concatenate([s.ravel(), sl.ravel()]))):
+        sm.set_reparam(ssm.SSM_INTERP_SPLINE, climb)
+        sm.set_string(x.reshape(s.shape) if sm is one else x)
+        assert sm.iterate(3, 0.1).tolist()[0] == 3
+        out.append(sm.get_string().reshape(-1)[:s.size])
+    assert torch.equal(out[0], out[1])
