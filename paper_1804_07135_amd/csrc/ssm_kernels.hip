@@ -804,7 +804,7 @@ __device__ __forceinline__ void conv_body_ct(const Prob& p, int s0, int G, cplx<
 constexpr int kConvU = 4;
 template <typename T, int MZ>
 __device__ __forceinline__ void conv_body(const Prob& p, int s0, int G, cplx<T>* __restrict__ X,
-                                          const T* __restrict__ nhat,
+                                          cplx<T>* __restrict__ Xo, const T* __restrict__ nhat,
                                           const cplx<T>* __restrict__ tw, cplx<T>* smem)
 {
     using V = cplx<T>;
@@ -816,7 +816,7 @@ __device__ __forceinline__ void conv_body(const Prob& p, int s0, int G, cplx<T>*
     V* lines = twl + 2 * my;
     load_twiddles(twl, lmy, f3y, tw);
     V* in = X + p.x_off + (long long)s0 * per;
-    V* out = X + p.xo_off + (long long)s0 * per;
+    V* out = Xo + p.xo_off + (long long)s0 * per;
     const int dy = kNT % ny, dr = kNT / ny;
     const int yb = threadIdx.x % ny, rb = threadIdx.x / ny;
     const int kx0 = s0 % nsl_img;
@@ -1097,6 +1097,31 @@ __device__ __forceinline__ void conv_body_ct3(const Prob& p, int s0, int G, cplx
     }
 }
 
+// The G slices from s0 that workgroup w of a problem takes (false: none).
+__device__ __forceinline__ bool conv_slices(const Prob& p, int w, int& s0, int& G)
+{
+    const int nsl_img = p.mx + 1, nsl = p.K * nsl_img;
+    if (p.xcd_remap) {
+        int kx, img;
+        if (SSM_CONV_XCD_REMAP) {
+            const int xcd = w & 7, j = w >> 3;
+            kx = (j / p.K) * 8 + xcd;
+            img = j % p.K;
+        } else {
+            kx = w / p.K;
+            img = w % p.K;
+        }
+        if (kx > p.mx || img >= p.K) return false;
+        s0 = img * nsl_img + kx;
+        G = 1;
+    } else {
+        s0 = w * p.gconv;
+        if (s0 >= nsl) return false;
+        G = min(p.gconv, nsl - s0);
+    }
+    return true;
+}
+
 template <typename T, int MZ, int BUILD>
 __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && MZ <= 8 ? SSM_CONV_WAVES_F32 : 1, 8))) void k_conv(const Prob* __restrict__ P, int np,
                                               const int* __restrict__ wstart,
@@ -1111,30 +1136,39 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     const Prob& p = problem(P, pi, wstart, done, w0, off);
     if (off) return;
     const int w = blockIdx.x - w0;
-    const int nsl_img = p.mx + 1, nsl = p.K * nsl_img;
     int s0, G;
-    if (p.xcd_remap) {
-        int kx, img;
-        if (SSM_CONV_XCD_REMAP) {
-            const int xcd = w & 7, j = w >> 3;
-            kx = (j / p.K) * 8 + xcd;
-            img = j % p.K;
-        } else {
-            kx = w / p.K;
-            img = w % p.K;
-        }
-        if (kx > p.mx || img >= p.K) return;
-        s0 = img * nsl_img + kx;
-        G = 1;
-    } else {
-        s0 = w * p.gconv;
-        if (s0 >= nsl) return;
-        G = min(p.gconv, nsl - s0);
-    }
+    if (!conv_slices(p, w, s0, G)) return;
     cplx<T>* sm = reinterpret_cast<cplx<T>*>(smem_);
     if constexpr (BUILD >= 16) conv_body_ct3<T, MZ, BUILD - 16>(p, s0, G, X, nhat, tw, sm);
     else if constexpr (BUILD > 0) conv_body_ct<T, MZ, BUILD>(p, s0, G, X, nhat, tw, sm);
-    else conv_body<T, MZ>(p, s0, G, X, nhat, tw, sm);
+    else conv_body<T, MZ>(p, s0, G, X, X, nhat, tw, sm);
+}
+
+// k_conv for FP64 problems of 9 to 16 layers.  Bound by the spills of its
+// z-phase (291 vector registers), so any scalar register kept meanwhile adds
+// to them: it leaves its arguments in memory (the build flag preloads those
+// before the first one passed by reference, KernargGap) and takes X' as an
+// array of its own.  k_conv's form, with both in registers (299 spilled) ->
+// this one, us a launch: 256 x 256 x 12, 8 images 2305 -> 2182; 100 x 100 x 12,
+// 16 images 1468 -> 1407; 40 x 40 x 9, 30 images 619 -> 604.  FP32 doesn't spill
+// and runs slower this way (256 x 256 x 12, 8 images 924 -> 940).
+struct KernargGap {
+    int a, b;
+};
+template <typename T, int MZ>
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(1, 8))) void k_conv_plain(
+    KernargGap, const Prob* __restrict__ P, int np, const int* __restrict__ wstart, cplx<T>* __restrict__ X,
+    cplx<T>* __restrict__ Xo, const T* __restrict__ nhat, const cplx<T>* __restrict__ tw, const int* __restrict__ done)
+{
+    extern __shared__ double2 smem_[];
+    const int pi = find_problem(wstart, np, blockIdx.x);
+    int w0;
+    bool off;
+    const Prob& p = problem(P, pi, wstart, done, w0, off);
+    if (off) return;
+    int s0, G;
+    if (!conv_slices(p, blockIdx.x - w0, s0, G)) return;
+    conv_body<T, MZ>(p, s0, G, X, Xo, nhat, tw, reinterpret_cast<cplx<T>*>(smem_));
 }
 
 // First pass of both halves of a line's padded y transform, for the inputs e
@@ -3329,6 +3363,9 @@ static void launch_conv_b(const Prob* P, int np, const WorkMap* wm, cplx<T>* x, 
         if constexpr (conv_halves(MZ, BUILD, sizeof(T)))
             hipLaunchKernelGGL((k_convh<MZ, BUILD>), dim3(w.total), dim3(kNT), convh_lds(BUILD, MZ), st, P, np,
                                w.start, x, nhat, t, done);
+        else if constexpr (sizeof(T) == 8 && MZ == 16)
+            hipLaunchKernelGGL((k_conv_plain<T, MZ>), dim3(w.total), dim3(kNT), lds, st, KernargGap{}, P, np, w.start,
+                               x, x, nhat, t, done);
         else
             hipLaunchKernelGGL((k_conv<T, MZ, BUILD>), dim3(w.total), dim3(kNT), lds, st, P, np, w.start, x, nhat, t,
                                done);
