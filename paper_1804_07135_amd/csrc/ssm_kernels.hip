@@ -1290,6 +1290,8 @@ __device__ __forceinline__ void conv_last_pass(const V* row0, int j, int ny, con
 //      is independent of x and y) and that first inverse pass;
 //   3. the last inverse pass of both halves, the second un-twiddled and added
 //      to the first, to global memory.
+// A value that is not finite is not independent of zeros: step 2 notes its
+// slice and step 3 makes z (x and y) NaN where x or y (z) had one.
 // m = 2^a = A B: radix-A and radix-B passes (step 2 takes A / B radix-B
 // transforms and one radix-A inverse transform per component).  m = 3 M:
 // A = 12 is the radix-3 step with the radix-4 pass of the three sub-lines, B =
@@ -1320,6 +1322,9 @@ __global__ __launch_bounds__(conv1_cfg(BUILD, sizeof(T)).nt)
     constexpr int F3 = BUILD >= 16, LMY = F3 ? BUILD - 16 : BUILD;
     static_assert(MY == (F3 ? 3 << LMY : 1 << LMY) && (!F3 || A == 12), "split does not match the length");
     extern __shared__ double2 smem_[];
+    // by wavefront: bit 2 g: an x or y value of slice g is not finite, 2 g + 1: z
+    __shared__ unsigned bad[NT / 64];
+    static_assert(C.g <= 16, "two bits a slice");
     const int pi = find_problem(wstart, np, blockIdx.x);
     int w0;
     bool off;
@@ -1392,6 +1397,7 @@ __global__ __launch_bounds__(conv1_cfg(BUILD, sizeof(T)).nt)
     __syncthreads();
 
     // step 2
+    unsigned nf = 0;
     if (it2 < n2) {
         // F3: twiddle of value j of a transform at output q / 3 of the first
         // pass
@@ -1402,6 +1408,12 @@ __global__ __launch_bounds__(conv1_cfg(BUILD, sizeof(T)).nt)
             for (int j = 1; j < B; ++j) tw1[j] = twl[6 * j * k];
         }
         V* const lg = lines + (gh2 >> 1) * 3 * LS + (gh2 & 1) * A;
+        // an input that is not finite leaves no frequency finite, nor then any
+        // output of the inverse transform (looked at where the registers
+        // allow it)
+        auto note = [&](const V& v, int c) {
+            if (!isfinite(v.x + v.y)) nf |= 1u << ((gh2 & ~1) + c / 2);
+        };
         auto forward = [&](int c, V (&v)[R]) {
             const V* col = lg + c * LS;
             if constexpr (F3) {
@@ -1429,6 +1441,7 @@ __global__ __launch_bounds__(conv1_cfg(BUILD, sizeof(T)).nt)
             }
 #pragma unroll
             for (int r = 0; r < R; ++r) settle(v[r]);
+            if constexpr (kEarly) note(v[0], c);
         };
         // F3: rows r of the same column; else row q, columns 0..A-1.  (The
         // lanes of one slice and half lie in one wavefront, which reads all
@@ -1437,6 +1450,7 @@ __global__ __launch_bounds__(conv1_cfg(BUILD, sizeof(T)).nt)
 #pragma unroll
             for (int r = 0; r < R; ++r) settle(v[r]);
             dft_reg<V, R, true>(v);
+            if constexpr (!kEarly) note(v[0], c);
             V* col = lg + c * LS;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -1473,6 +1487,9 @@ __global__ __launch_bounds__(conv1_cfg(BUILD, sizeof(T)).nt)
             inverse(2, x);
         }
     }
+    if (__any(nf))
+        for (int o = 32; o > 0; o >>= 1) nf |= __shfl_xor(nf, o);
+    if ((threadIdx.x & 63) == 0) bad[threadIdx.x >> 6] = nf;
     __syncthreads();
 
     // step 3, onto the slice.  F3: item (line, j), y = j + B (r + 4 t) from
@@ -1482,6 +1499,16 @@ __global__ __launch_bounds__(conv1_cfg(BUILD, sizeof(T)).nt)
         const int line = it / N3, j = it & (N3 - 1), g = line / 3;
         conv_last_pass<V, A, B, F3>(lines + line * LS, j, ny, twl, x0 + g * istr + (line - 3 * g) * ny);
     }
+    nf = bad[0];
+#pragma unroll
+    for (int wv = 1; wv < NT / 64; ++wv) nf |= bad[wv];
+    if (nf)  // the vanishing xz and yz times a value that is not finite, over the thread's own results
+        for (int it = threadIdx.x; it < G * 3 * N3; it += NT) {
+            const int line = it / N3, j = it & (N3 - 1), g = line / 3, c = line - 3 * g;
+            V* dst = x0 + g * istr + c * ny;
+            if ((nf >> (2 * g)) & (c == 2 ? 1 : 2))
+                for (int y = j; y < ny; y += N3) dst[y].x = dst[y].y = __builtin_nanf("");
+        }
 }
 
 // ---------------------------------------------------------------------------
