@@ -517,8 +517,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 // result goes to the output slice and the y half 1 result is added onto it
 // (each thread adds onto the values it stored itself).  The kernel
 // spectrum carries 1/(Px Py Pz).
-// Serves what the kernels below don't: 5 to 8 layers at the y lengths k_convz
-// can't hold, 9 to 16 layers, and y lengths without a compile-time build.
+// Serves what the kernels below don't: 5 to 8 layers where conv_inplace says so,
+// 9 to 16 layers, and y lengths without a compile-time build.
 // LDS: twiddles (2 m_y) + G*3*nz lines of m_y.
 // ---------------------------------------------------------------------------
 
