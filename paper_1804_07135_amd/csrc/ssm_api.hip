@@ -260,7 +260,7 @@ void apply_tiles(Prob& p, const Tiles& t, size_t tsize)
     p.ytf = t.ytf;
     p.ntyf = (p.ny + p.ytf - 1) / p.ytf;
     p.tilesf = p.nz * p.ntyf;
-    p.wgf = pad8((p.csplit ? 3 : 1) * p.K * p.tilesf);
+    p.wgf = pad8(p.K * p.tilesf);  // (build_plan: with csplit three times the items)
     p.yt = t.yt;
     p.nty = (p.ny + p.yt - 1) / p.yt;
     p.tiles = p.nz * p.nty;
@@ -278,6 +278,31 @@ void apply_tiles(Prob& p, const Tiles& t, size_t tsize)
         const int n = (p.K + g - 1) / g;
         p.gconv = (p.K + n - 1) / n;
     }
+}
+
+// Whether the workgroups of a forward x launch take one component each (three
+// times the workgroups, each with a third of the chain) or all three one after
+// another: one where that takes fewer rounds of the workgroups that the chip
+// holds at once (3 or, in FP32, 4 to a CU).  Elsewhere, and in launches of
+// several rounds, the twiddle loads and barriers it repeats cost more than it
+// gives.  w0, w1: workgroups with all three, with one; lds: bytes of each.
+// An iteration's time with one less that with all three, us, by w0 over the
+// workgroups the chip holds:
+//   FP32 0.14 90 x 90 x 3, 4 images -4.1; 0.39 112 x 112, 100 images -3.7; 0.62
+//   64 x 64 x 4, 20 images -0.1; 0.70 100 x 75 x 3, 24 images +1.8; 0.98 32 x 32, 1000
+//   images +2.9; 1.17 200 x 180 x 5, 20 images -2.8; 1.56 250 x 250 x 5, 20 images
+//   -4.0; 2.34 180 x 180, 200 images -3.0; 3.75 180 x 180 x 8, 40 images +7.3
+//   FP64 0.52 64 x 64, 200 images -1.1; 0.83 32 x 32 x 4, 20 images +1.7; 0.94 100 x
+//   75 x 3, 24 images +2.6; 1.04 64 x 64, 400 images -4.2; 1.33 64 problems of 32 x
+//   32, 10 images -6.9; 1.67 128 x 128 x 8, 20 images -1.4; 2.08 250 x 250 x 5, 10
+//   images +1.6; 6.67 250 x 250 x 8, 20 images +12; with the radix-3 twiddles of
+//   lengths 3 2^a 1.41 90 x 90 x 3, 60 images -1.3; 1.80 180 x 180, 60 images +0.9
+bool xfwd_split(long long w0, long long w1, size_t lds, size_t tsize, bool f3)
+{
+    if (w0 == 0) return false;
+    const long long chip = 256LL * std::max<long long>(1, std::min<long long>(tsize == 4 ? 4 : 3, kLdsMax / lds));
+    const auto rounds = [&](long long w) { return (w + chip - 1) / chip; };
+    return 2 * w0 <= chip * (tsize == 4 ? 5 : f3 ? 3 : 4) && rounds(w1) < 3 * rounds(w0);
 }
 
 // the inverse x transform's kind: x length kind, or the wide workgroups
@@ -336,14 +361,6 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         p.nhz = q.nz > 1 ? 2 : 1;
         p.N = (long long)q.nx * q.ny * q.nz;
         p.conv1 = conv_inplace(p.nz, p.mz, conv_build(p.mz, p.lmy, p.f3y), (int)pl.tsize);
-        // one component per forward x workgroup on small launches: shorter
-        // chains and more workgroups (64 x 64, 20 images, FP32: 11.0 -> 7.4
-        // us; 250 x 250 x 3, 20 images: 43 -> 37; with the longer chain of
-        // lengths 3 2^a still 64 lattices of 72 x 72, 16 images: 76 -> 67);
-        // on larger ones the twiddle loads and barriers it repeats cost more
-        // (256 x 256 x 4, 32 images: 63 -> 68; 256 x 256 x 8, 48 images: 181
-        // -> 189, FP64 390 -> 415)
-        p.csplit = batch_rows * p.mx < (p.f3x ? 1 << 24 : 1 << 22) ? 1 : 0;
         const Tiles t = tiles ? (*tiles)[i] : default_tiles(p, pl.tsize, batch_rows, batch_slices);
         apply_tiles(p, t, pl.tsize);
         pl.tiles.push_back(t);
@@ -423,6 +440,20 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
     }
     for (Prob& q : pl.P)
         if (!q.conv1) q.xo_off += xo;
+    for (int k = 0; k < 2; ++k) {
+        long long w0 = 0, w1 = 0;
+        for (const Prob& q : pl.P)
+            if (q.f3x == k) {
+                w0 += q.wgf;
+                w1 += pad8(3 * q.K * q.tilesf);
+            }
+        if (!xfwd_split(w0, w1, pl.lds_xf, pl.tsize, k == 1)) continue;
+        for (Prob& q : pl.P)
+            if (q.f3x == k) {
+                q.csplit = 1;
+                q.wgf = pad8(3 * q.K * q.tilesf);
+            }
+    }
     // kernel-spectrum offsets per shape
     std::vector<long long> nh_off(pl.shapes.size());
     long long nh = 0;
