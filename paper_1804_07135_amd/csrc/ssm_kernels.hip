@@ -3957,7 +3957,10 @@ __global__ __launch_bounds__(kNT) void k_interp_spline(const Prob* __restrict__ 
 // and the climbing image are copied.  With lin (skip flags), the problems
 // whose spline is degenerate take the linear step here too, so that batches
 // of such problems alone need no launch of k_interp, which otherwise comes
-// after (64 problems of 48..96 sites, 16 images: 7 us of an iteration).
+// after (64 problems of 48..96 sites, 16 images: 7 us of an iteration).  That
+// linear step, us, k_interp -> here (one image after another, where each waited
+// on memory, in brackets): FP32 64 x 64, 30 images 12.6 -> 9.2 (29.4), 64 problems of
+// 72 x 72, 16 images 29.0 -> 23.7 (38.1); FP64 112 x 112, 16 images 13.5 -> 11.3 (18.1).
 template <typename T, int KMAX>
 __global__ __launch_bounds__(kNT) void k_interp_splw(const Prob* __restrict__ P, int np,
                                                      const int* __restrict__ wstart, const T* __restrict__ ss,
@@ -3979,19 +3982,35 @@ __global__ __launch_bounds__(kNT) void k_interp_splw(const Prob* __restrict__ P,
         if (i >= N) return;
         const T* src = ss + p.s_off + i;
         T* dst = s + p.s_off + i;
-        for (int k = 0; k < K; ++k) {
-            const bool copy = lin[pi] || k == 0 || k == K - 1 || k == kci;
-            const T* a = src + (long long)(copy ? k : jidx[g0 + k]) * Ms;
-            T ta[3], tb[3], to[3];
+        // rounds of U images, whose loads are issued together (an image past
+        // the last repeats it and stores nothing)
+        constexpr int U = sizeof(T) == 4 ? 8 : 4;
+        const bool still = lin[pi];
+#pragma unroll 1
+        for (int k0 = 0; k0 < K; k0 += U) {
+            T ta[U][3], tb[U][3];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                ta[c] = a[c * N];
-                tb[c] = copy ? ta[c] : a[Ms + c * N];
-                to[c] = ta[c];
+            for (int u = 0; u < U; ++u) {
+                const int k = min(k0 + u, K - 1);
+                const bool copy = still || k == 0 || k == K - 1 || k == kci;
+                const T* a = src + (long long)(copy ? k : jidx[g0 + k]) * Ms;
+                const T* b = copy ? a : a + Ms;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    ta[u][c] = a[c * N];
+                    tb[u][c] = b[c * N];
+                }
             }
-            if (!copy) interp_site<T>(ta, tb, wgt[g0 + k], to, flags);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) dst[k * Ms + c * N] = to[c];
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + u;
+                if (k >= K) continue;
+                const bool copy = still || k == 0 || k == K - 1 || k == kci;
+                T to[3] = {ta[u][0], ta[u][1], ta[u][2]};
+                if (!copy) interp_site<T>(ta[u], tb[u], wgt[g0 + k], to, flags);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) dst[k * Ms + c * N] = to[c];
+            }
         }
         return;
     }

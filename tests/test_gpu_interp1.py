@@ -59,3 +59,28 @@ def test_spline_pass_takes_degenerate_splines(precision, climb, kind):
         assert sm.iterate(3, 0.1).tolist()[0] == 3
         out.append(sm.get_string().reshape(-1)[:s.size])
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("precision,K", [(ssm.SSM_FP64, 3), (ssm.SSM_FP64, 5), (ssm.SSM_FP64, 16),
+                                         (ssm.SSM_FP32_MIXED, 8), (ssm.SSM_FP32_MIXED, 9), (ssm.SSM_FP32_MIXED, 30)])
+@pytest.mark.parametrize("nx,ny", [(20, 18), (17, 31), (16, 31)])
+def test_degenerate_splines_in_rounds_of_images(precision, K, nx, ny):
+    """The same at image counts on both sides of the pass's rounds and on
+    lattices of several workgroups, the last one ragged, whose sites k_interp
+    takes four (two in FP64) or one to a thread; the degenerate problem second in its
+    batch, behind one whose spline is not."""
+    p = dict(nx=nx, ny=ny, nz=1, K=K, J=0.9, d=0.35, ku=0.21, D=0.02)
+    s = inputs.random_unit_spins((K, 3, 1, ny, nx), seed=K)
+    s[1] = s[0]  # two equal neighbours
+    first = dict(p, nx=11, ny=5, K=7)
+    sf = inputs.random_unit_spins((7, 3, 1, 5, 11), seed=2)
+    long = dict(p, nx=3, ny=2, K=40)
+    sl = inputs.random_unit_spins((40, 3, 1, 2, 3), seed=1)
+    out = []
+    for probs, x in (([first, p], [sf, s]), ([first, p, long], [sf, s, sl])):
+        sm = ssm.StringMethod(probs, precision)
+        sm.set_reparam(ssm.SSM_INTERP_SPLINE, False)
+        sm.set_string(np.concatenate([v.ravel() for v in x]))
+        sm.iterate(1, 0.0)  # (no step: the spline stays degenerate)
+        out.append(sm.get_string().reshape(-1)[:sf.size + s.size])
+    assert torch.equal(out[0], out[1])
