@@ -148,7 +148,9 @@ size_t lds_xinv(const Prob& p, int yt, size_t tsize)
 
 // whether (and in how much LDS) the two-step inverse x transform serves tiles
 // of yt rows: its three components' lines, with the tile's real field over
-// them afterwards
+// them afterwards, where that leaves three workgroups to a CU (with two, FP64
+// rows of 33 sites in the default tiles of 32, it is slower than one component
+// at a time in three: 33 x 33, 300 images 29.7 us against 25.6)
 bool xinv2_tile(const Prob& p, int yt, size_t tsize, size_t& lds)
 {
     if (!xinv2_len(p.lmx, p.f3x, (int)tsize)) return false;
@@ -158,7 +160,7 @@ bool xinv2_tile(const Prob& p, int yt, size_t tsize, size_t& lds)
     const size_t lines = (size_t)3 * hp * xinv2_line(c, hp, (int)tsize) * 2 * tsize;
     const size_t field = (size_t)3 * yt * xinv2_hrow(p.nx, hp) * tsize;
     lds = std::max(lines, field) + (xinv2_twlds(p.mx, p.f3x, (int)tsize) ? 4 * p.mx * tsize : 0);
-    return lds <= kLdsMax / 2;
+    return lds <= kLdsMax / 3;
 }
 
 // most slices of a workgroup of k_convz: as many as leave three workgroups to
