@@ -183,7 +183,7 @@ size_t lds_convg(const Prob& p, int G, size_t tsize)
     if (p.conv1 == 2) return convz_lds(build, std::min(G, convz_gmax(p, tsize)), p.nz, (int)tsize);
     const int n = G * 3 * p.nz * p.my;
     if (conv_ct_shape(p.mz, p.lmy, p.f3y) || conv_ct3_shape(p.mz, p.lmy, p.f3y))
-        return (size_t)(2 * p.my + padded_len(n, conv_padl(p.mz, p.lmy, p.f3y, (int)tsize))) * 2 * tsize;
+        return (size_t)(2 * p.my + padded_len(n, conv_padl(p.mz, p.lmy, p.f3y))) * 2 * tsize;
     return (size_t)(2 * p.my + lds_padded_size(n)) * 2 * tsize;
 }
 

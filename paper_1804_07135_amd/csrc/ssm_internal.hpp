@@ -148,13 +148,10 @@ __host__ __device__ constexpr bool conv_inplace_min(int mz, int build, int tsize
 #ifndef SSM_CONV3_PADL
 #define SSM_CONV3_PADL 4
 #endif
-// the 3 2^a layouts of the FP32 form: one pad per 8 elements (fewer bank
+// the x kernels' 3 2^a layout in FP32: one pad per 8 elements (fewer bank
 // conflicts on its 8-byte elements; FP64 keeps one per 16)
 #ifndef SSM_X3_PADL_F32
 #define SSM_X3_PADL_F32 3
-#endif
-#ifndef SSM_CONV3_PADL_F32
-#define SSM_CONV3_PADL_F32 3
 #endif
 // x lengths with compile-time passes: powers of two 32..512 (lm = log2 m)
 // and 3 2^lm for 48..384, in the pad-SSM_X_PADL layout (3 2^lm in FP32:
@@ -167,10 +164,10 @@ __host__ __device__ constexpr int x_padl(int lm, int f3, int tsize)
            : x_ct3_len(lm, f3) ? pad_for(tsize == 4 ? SSM_X3_PADL_F32 : SSM_X_PADL, lm)
                                : 0;
 }
-__host__ __device__ constexpr int conv_padl(int mz, int lmy, int f3y, int tsize)
+__host__ __device__ constexpr int conv_padl(int mz, int lmy, int f3y)
 {
     return conv_ct_shape(mz, lmy, f3y)    ? pad_for(SSM_CONV_PADL, lmy)
-           : conv_ct3_shape(mz, lmy, f3y) ? pad_for(tsize == 4 ? SSM_CONV3_PADL_F32 : SSM_CONV3_PADL, lmy)
+           : conv_ct3_shape(mz, lmy, f3y) ? pad_for(SSM_CONV3_PADL, lmy)
                                           : 0;
 }
 // The inverse x kernel's transform in two register steps (xinv_two_step), for

@@ -568,8 +568,8 @@ __device__ __forceinline__ void conv_zcolumn(const Prob& p, int kx, int hy, int 
         // the same spectrum up to the sign of the z-odd components xz
         // and yz (the tensor is even in z except for those), so each
         // column reads only the rows r <= mirror (9 of 16 for MZ = 8)
-        // and the unrolled loop folds the repeated loads (not for 8
-        // layers with y lengths below 256, where keeping the shared rows
+        // and the unrolled loop folds the repeated loads (MIR; not in
+        // k_conv at y lengths below 256, where keeping the shared rows
         // live costs more registers than it saves)
         constexpr bool kMir = SSM_CONV_NH_MIRROR && MIR;
         T nv[MZ][6];
@@ -652,12 +652,13 @@ __device__ __forceinline__ void conv_zphase(const Prob& p, int G, int kx0, int h
         while (kx >= nsl_img) kx -= nsl_img;
         // padded offsets: the column's first % 2^PADL = py % 2^PADL and the
         // line offsets are multiples of the line length, so padx distributes
-        conv_zcolumn<T, MZ, LMY, F3, (MZ <= 4 || LMY >= 8), false>(p, kx, hy, qy, lines + padx<PADL>(g * 3 * nz * MY + py), padx<PADL>(MY), nhat,
-                                     tw);
+        conv_zcolumn<T, MZ, LMY, F3, (LMY >= 8), false>(p, kx, hy, qy, lines + padx<PADL>(g * 3 * nz * MY + py),
+                                                        padx<PADL>(MY), nhat, tw);
     }
 }
 
-// Compile-time-length body (m_y = 2^LMY) of the convolution of G slices.
+// Compile-time-length body (m_y = 2^LMY: 256, FP64 also 128; 8 padded layers, the
+// in-place kernels and k_convh take the rest) of the convolution of G slices.
 // The forward y transform takes its first pass straight from the slice in
 // global memory (zero beyond ny, the odd-half twiddle W^{hy*y} applied on
 // the way) and the inverse writes its last pass straight to the output
@@ -677,9 +678,10 @@ __device__ __forceinline__ void conv_body_ct(const Prob& p, int s0, int G, cplx<
     constexpr int B0 = fft_next_bits(LMY, MB), R0 = 1 << B0;
     constexpr int LNSL = fft_last_lns(LMY, MB);
     constexpr int BL = LMY - LNSL, RL = 1 << BL;
+    static_assert(MZ == 8 && !conv_inplace_all(MZ, LMY, sizeof(T)), "no other shape comes here");
     static_assert(LNSL >= B0, "the y schedule needs at least two passes");
     // pad layout; twiddles W_{2 m_y} from an LDS copy
-    constexpr int PADL = conv_padl(MZ, LMY, 0, sizeof(T));
+    constexpr int PADL = conv_padl(MZ, LMY, 0);
     constexpr int TWS = 0;
     // swizzled handoff between the two radix-16 passes of length 256
     constexpr bool SW = SSM_CONV_SWZ && PADL == 0 && LMY == 8 && MB == 4;
@@ -948,8 +950,8 @@ __device__ __forceinline__ void conv_body(const Prob& p, int s0, int G, cplx<T>*
     }
 }
 
-// Compile-time-length body for y lengths m_y = 3 M, M = 2^LMY (48, 96,
-// 192).  As conv_body_ct, with the radix-3 steps of the y transform
+// Compile-time-length body for y lengths m_y = 3 M, M = 2^LMY (192 in FP64; 8
+// padded layers).  As conv_body_ct, with the radix-3 steps of the y transform
 // (ssm_fft.hpp) fused into the global-memory side: the forward one reads
 // the slice (zero beyond ny, the odd-half twiddle applied), does the radix-3
 // butterflies and the first, radix-4 pass of the three sub-lines, and
@@ -969,7 +971,8 @@ __device__ __forceinline__ void conv_body_ct3(const Prob& p, int s0, int G, cplx
     constexpr int BF = 2, RF = 1 << BF;  // fused sub-line passes: radix 4
     constexpr int QF = M / RF;           // their butterflies per sub-line
     constexpr int LQF = LMY - BF;
-    constexpr int PADL = conv_padl(MZ, LMY, 1, sizeof(T));
+    constexpr int PADL = conv_padl(MZ, LMY, 1);
+    static_assert(MZ == 8 && !conv_inplace_all(MZ, 16 + LMY, sizeof(T)), "no other shape comes here");
     static_assert(PLG >= 1 && LMY - BF >= 2, "length outside the compile-time 3 2^a set");
     const int nsl_img = p.mx + 1;
     const int nz = p.nz, ny = p.ny;
@@ -1596,7 +1599,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     // z-phase: item (slice, half, frequency)
     for (int it = threadIdx.x; it < G * 2 * MY; it += kNT) {
         const int gh = it / MY, f = it - gh * MY, hy = gh & 1, r = f / A, q = f - r * A;
-        conv_zcolumn<T, MZ, LMY, F3, true, (MZ == 8 && MY < 256)>(p, kx, hy, f, lines + (gh >> 1) * L * LS + r * JS + hy * A + q, LS, nhat, tw);
+        conv_zcolumn<T, MZ, LMY, F3, true, MZ == 8>(p, kx, hy, f, lines + (gh >> 1) * L * LS + r * JS + hy * A + q,
+                                                    LS, nhat, tw);
     }
     __syncthreads();
 
@@ -2136,7 +2140,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT > kNT ? 4
         hrow = xinv2_hrow(nx, hp);
         auto run = [&](auto lmc) {
             constexpr int LM = decltype(lmc)::value;
-            if constexpr (NT > kNT ? !F3 && (LM == 5 || (LM == 6 && sizeof(T) == 4)) : true)
+            if constexpr ((NT > kNT) == xinv2_wide(LM, F3, (int)sizeof(T)))
                 xinv_two_step<T, F3, LM, NT>(Xi, lines, hd, twl, tw, z, y0, hp, lhp, nx, nz, ny, hrow);
         };
         switch (lm) {
@@ -2151,7 +2155,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT > kNT ? 4
         hrow = nx;
         load_twiddles(twl, lm, f3, tw);
         __syncthreads();
-    #pragma unroll 1
+#pragma unroll 1
         for (int c = 0; c < 3; ++c) {
             // kXinvU items per thread per round: their loads are issued
             // together (no load sits under a branch; an item past the end loads
@@ -2169,7 +2173,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT > kNT ? 4
                     if (k >= nx) continue;
                     const int ie = (2 * rp) * m + k, io = ie + m;
                     V e[3], o[3];
-    #pragma unroll
+#pragma unroll
                     for (int t = 0; t < 3; ++t) {
                         const int a = ie + t * M, b = io + t * M;
                         e[t] = lines[a + (a >> psh)];
@@ -2178,7 +2182,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT > kNT ? 4
                     const V w1 = twl[2 * k], w2 = twl[4 * k];
                     radix3_bfly<true>(e[0], e[1], e[2], w1, w2);
                     radix3_bfly<true>(o[0], o[1], o[2], w1, w2);
-    #pragma unroll
+#pragma unroll
                     for (int t = 0; t < 3; ++t) {
                         const int x = k + t * M;
                         if (x < nx) {
