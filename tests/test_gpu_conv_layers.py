@@ -58,3 +58,23 @@ def test_halves_kernel_edges(oracle, ny, nz):
     both = ssm.StringMethod([q, p], ssm.SSM_FP64)
     hb = both.eval(torch.cat([torch.as_tensor(s2).reshape(-1), torch.as_tensor(s).reshape(-1)]))[1]
     assert torch.equal(hb.reshape(-1)[-h.numel():].cpu(), h.reshape(-1).cpu())
+
+
+@pytest.mark.parametrize("ny", [130, 192, 194, 256])
+def test_halves_kernel_four_layers(oracle, ny):
+    """FP64, 4 layers, the one layer count that k_convh serves (3 layers of these
+    lengths fit in k_convz): the shortest even and the whole lines of both its
+    lengths, more images than XCDs, alone and beside a problem of 3 layers."""
+    K = 9
+    p = dict(nx=2, ny=ny, nz=4, K=K, J=0.9, d=0.35, ku=0.21, D=0.4)
+    s = inputs.random_unit_spins((K, 3, 4, ny, 2), seed=ny)
+    h = ssm.StringMethod(p, ssm.SSM_FP64).eval(s)[1]
+    for k in (0, K - 1):
+        ho = oracle.field(s[k], p["J"], p["d"], p["ku"], p["D"])
+        assert np.abs(h[k].cpu().numpy() - ho).max() < 1e-10 * np.abs(ho).max(), k
+    q = dict(p, nz=3, K=2)
+    s2 = inputs.random_unit_spins((2, 3, 3, ny, 2), seed=1)
+    h2 = ssm.StringMethod(q, ssm.SSM_FP64).eval(s2)[1]
+    both = ssm.StringMethod([q, p], ssm.SSM_FP64)
+    hb = both.eval(torch.cat([torch.as_tensor(s2).reshape(-1), torch.as_tensor(s).reshape(-1)]))[1].reshape(-1)
+    assert torch.equal(hb[:h2.numel()], h2.reshape(-1)) and torch.equal(hb[h2.numel():], h.reshape(-1))

@@ -61,3 +61,31 @@ def test_wide_workgroups(oracle, precision, nx, ny, nz):
     Eb, hb = batch.eval(np.concatenate([so[0].ravel(), s.ravel(), so[1].ravel()]))[:2]
     assert torch.equal(Eb[2:5], E)
     assert torch.equal(hb.reshape(-1)[so[0].size:so[0].size + s.size], h.reshape(-1))
+
+
+@pytest.mark.parametrize("precision,nx", [(ssm.SSM_FP64, 17), (ssm.SSM_FP64, 31), (ssm.SSM_FP64, 32),
+                                          (ssm.SSM_FP32_MIXED, 17), (ssm.SSM_FP32_MIXED, 32), (ssm.SSM_FP32_MIXED, 49),
+                                          (ssm.SSM_FP32_MIXED, 63), (ssm.SSM_FP32_MIXED, 64)])
+@pytest.mark.parametrize("ny,nz", [(33, 1), (1, 2), (7, 3), (64, 2)])
+def test_wide_workgroup_lengths(oracle, precision, nx, ny, nz):
+    """Every length that takes workgroups of kXinvWide threads (half lengths 32
+    and, FP32, 64) at its shortest and longest rows, odd and even row counts
+    and several layers: field and energy against the oracle, and bitwise the
+    same beside problems of the other kinds (the rest of test_wide_workgroups'
+    rows take 256 threads)."""
+    p = dict(nx=nx, ny=ny, nz=nz, K=2, J=0.9, d=0.35, ku=0.21, D=0.4)
+    s = inputs.random_unit_spins((2, 3, nz, ny, nx), seed=nx + ny)
+    if precision == ssm.SSM_FP32_MIXED:
+        s = s.astype(np.float32).astype(np.float64)
+    E, h = ssm.StringMethod(p, precision).eval(s)[:2]
+    for k in range(2):
+        ho = oracle.field(s[k], p["J"], p["d"], p["ku"], p["D"])
+        assert np.abs(h[k].cpu().numpy() - ho).max() < TOL[precision] * np.abs(ho).max(), k
+        scale = 0.5 * np.abs(s[k] * ho).sum()
+        assert abs(E[k].item() + 0.5 * (s[k] * ho).sum()) < TOL[precision] * scale, k
+    others = [dict(p, nx=40), dict(p, nx=110)]
+    so = [inputs.random_unit_spins((2, 3, nz, ny, q["nx"]), seed=5) for q in others]
+    batch = ssm.StringMethod([others[0], p, others[1]], precision)
+    Eb, hb = batch.eval(np.concatenate([so[0].ravel(), s.ravel(), so[1].ravel()]))[:2]
+    assert torch.equal(Eb[2:4], E)
+    assert torch.equal(hb.reshape(-1)[so[0].size:so[0].size + s.size], h.reshape(-1))
