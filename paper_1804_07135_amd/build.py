@@ -19,7 +19,9 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed FP32 instructions stay off: plain VALU FP32 only
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # the first kernel arguments arrive in registers instead of by a load
+    # the first kernel arguments arrive in registers instead of by a load: 40
+    # iterations of 32x32, 10 images, FP64 1051 -> 1037 us, 5 iterations of
+    # 200x180x5, 20 images, FP32 1650 -> 1634
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-I", INCLUDE, "-I", CSRC,
 ]

@@ -22,7 +22,7 @@ __host__ __device__ constexpr int tw_off(int lg, int f3)
     return f3 ? (4 << kMaxLogM) - 2 + 6 * ((1 << lg) - 1) : (2 << lg) - 2;
 }
 constexpr int kTwCompact = tw_off(9, 1);  // entries of the compact table
-constexpr int kNT = 256;       // threads per workgroup for every kernel
+constexpr int kNT = 256;       // threads per workgroup (k_conv1: Conv1Cfg::nt; k_xinv of short rows: kXinvWide)
 constexpr int kConvElems = 24 * kNT;  // complex values per convolution workgroup (slice batching cap)
 constexpr int kArcEPT = 8;     // flat elements per thread in the arc-length kernel
 constexpr int kNTerm = 5;      // energy partial slots: E, T_J, T_d, T_ku, T_dip
@@ -35,11 +35,11 @@ constexpr int kMaxImages = 1024;  // images per problem (the ABI's limit)
 #endif
 constexpr int kRed1MaxK = 64, kRed1MaxPart = 256, kRedLanes = SSM_RED_LANES;
 
-// The convolution kernel comes in two builds: one with compile-time-length
-// bodies for y lengths 32..256 and up to 8 layers, one with a runtime-length
-// body for every other shape.  They are separate kernels so that each gets
-// its own register allocation; a launch covers a problem with whichever
-// build serves its shape.
+// The convolution has a build for each compile-time y length (32..256 and 48,
+// 96, 192; up to 8 layers) and one with a runtime length for every other shape.
+// They are separate kernels so that each gets its own register allocation; a
+// launch covers a problem with whichever serves its shape (conv_inplace and
+// conv_halves: which kernel of a build).
 #ifndef SSM_CONV_CT
 #define SSM_CONV_CT 1
 #endif
@@ -95,8 +95,8 @@ __host__ __device__ constexpr size_t convz_lds(int build, int G, int nz, int tsi
 }
 
 // k_convh (FP64, 4 padded layers, one half at a time, one slice to a
-// workgroup): where it serves the slices that k_convz doesn't hold, and LDS for
-// up to nz layers
+// workgroup): where it serves the slices that k_convz doesn't hold (4 layers of
+// 192 and 256 points), and LDS for up to nz layers
 __host__ __device__ constexpr bool conv_halves(int mz, int build, int tsize)
 {
     return tsize == 8 && mz == 4 && build > 0;
@@ -114,7 +114,9 @@ __host__ __device__ constexpr size_t convh_lds(int build, int nz)
 // than k_conv's three (256 x 256 x 8) or, in FP64, not fit.  But not 5 and 6 layers
 // of 256 points (FP32), where k_conv is the faster with its three workgroups
 // (us a launch, k_convz -> k_conv: 250 x 250 x 5, 20 images 206 -> 201, 100 x 250
-// x 5, 20 images 111 -> 99, 250 x 250 x 6, 30 images 396 -> 375).  3 layers of
+// x 5, 20 images 111 -> 99, 250 x 250 x 6, 30 images 396 -> 375; an iteration is 1 to
+// 7% shorter with it, but 3% longer for 250 x 250 x 5, 20 images, whose X fits the
+// last-level cache by itself but not with X').  3 layers of
 // 256 points in FP64 go the other way (250 x 250 x 3, 20 images: k_convz 208,
 // k_convh 273, k_conv 377; of 192 points, 180 x 180 x 3, 20 images: 112, 147, 172).
 // (_all, _min: every layer count, the smallest one, of a padded count mz.)
@@ -253,7 +255,7 @@ struct Prob {
     int csplit;            // 1: a forward x workgroup takes one component of its tile, else all three
     int img0;              // index of this problem's first image in batch-wide arrays
     int gconv;             // (image, kx) slices per convolution workgroup: consecutive ones (kx fastest),
-                           // or images of one kx (monolayers)
+                           // or images of one kx (in place)
     int conv1;             // convolution in place, both halves together: 1 by k_conv1, 2 by k_convz
     int xi2;               // inverse x transform by xinv_two_step: 1, or 2 with kXinvWide threads
     int arc_chunks;        // arc-length workgroups (flat chunks of 3N) per image
@@ -262,7 +264,7 @@ struct Prob {
     long long s_off;       // element offset of image 0 in spin / field buffers
     long long x_off;       // complex-element offset in the x-spectrum buffer X
     long long xo_off;      // offset of the convolved spectra from the same base: x_off where the
-                           // convolution works in place (monolayers), in X' after X otherwise
+                           // convolution works in place (conv1), in X' after X otherwise
     long long nh_off;      // element offset of this shape's dipole-kernel spectrum
     long long ep_off;      // offset (doubles) of energy partials: [K][tiles][kNTerm]
     long long ap_off;      // offset (doubles) of arc partials: [K][arc_chunks*4]
@@ -282,7 +284,7 @@ struct Prob {
 struct WorkMap {
     int* start;      // device: [nprob + 1] prefix sums of workgroup counts
     int total;
-    size_t lds;      // dynamic LDS bytes (inverse x, monolayer convolution builds)
+    size_t lds;      // dynamic LDS bytes (inverse x, in-place convolution builds)
 };
 
 // ------------------------------------------------------------------------

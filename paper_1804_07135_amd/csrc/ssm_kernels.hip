@@ -1,7 +1,8 @@
 // HIP kernels (gfx950) of the simplified string method for atomistic spin
 // lattices (Heistracher et al., arXiv:1804.07135).
 //
-// One string iteration is six kernels over every image of every problem:
+// One string iteration is five or six kernels over every image of every
+// problem:
 //   k_xfwd   zero-padded real-to-complex FFT along x of the three spin
 //            components (Sec. II.A: the dipolar field of eq. (6) is a
 //            circular convolution once the lattice is padded);
@@ -9,8 +10,8 @@
 //            the FFT of the point-dipole tensor of eq. (7), inverse FFTs
 //            (k_conv1 for monolayers and k_convz for several layers, in
 //            place, where a slice fits in LDS with both halves of its padded
-//            y transform; k_convh and k_conv, one half after the other, where
-//            it doesn't);
+//            y transform; k_convh, k_conv and k_conv_plain, one half after the
+//            other, elsewhere);
 //   k_xinv   inverse FFT along x, then per site: exchange, DMI and
 //            anisotropy stencils (eqs. (3)-(5)), the energy -1/2 h.s of
 //            eq. (8) reduced in FP64, and the projected descent step with
@@ -134,9 +135,9 @@ __device__ __forceinline__ int find_problem(const int* __restrict__ start, int n
 // value from each cache line of the descriptor is loaded together with the
 // two others, ahead of the branch on done, so that a kernel starts after one
 // memory latency instead of three in a row (the fields it uses later then
-// come from the scalar cache).  With the kernel arguments preloaded into
-// registers (a build flag) and Prob::csplit: 64 x 64, 20 images, FP32 2.04 ->
-// 1.85 ms per 40 iterations; 32 x 32, 10 images, FP64 1.60 -> 1.45 ms.
+// come from the scalar cache).  Against the loads one after another: 40
+// iterations of 32 x 32, 10 images, FP64 1062 -> 1037 us; of 64 x 64, 20 images, FP32
+// 1372 -> 1351; dynamics of 100 x 75 x 3, 24 images, FP64 2927 -> 2886.
 __device__ __forceinline__ const Prob& problem(const Prob* __restrict__ P, int pi, const int* __restrict__ wstart,
                                                const int* __restrict__ done, int& w0, bool& off)
 {
@@ -1304,9 +1305,10 @@ __device__ __forceinline__ void conv_last_pass(const V* row0, int j, int ny, con
 // The multi-layer bodies with one layer took each half by itself, through
 // five LDS round trips and workgroup barriers, reading X twice and reading
 // back and adding to X'.  Measured (us a launch, FP32 unless said): 64
-// lattices of 48..96 sites, 16 images, 272 -> 121; 112 x 112, 60 images, 39 ->
-// 21 and 240 images 113 -> 56 (FP64: 320 -> 118); 32 x 32, 10 images, FP64,
-// 12.5 -> 6.7.  What bounds it now is vector arithmetic and LDS in about
+// lattices of 48..96 sites, 16 images, three launches 272 -> 121; 112 x 112, 60
+// images 39 -> 20 and 240 images 113 -> 53 (FP64 320 -> 130); 32 x 32, 10 images,
+// FP64 12.5 -> 5.6.  Noting the values that are not finite is 1 to 2
+// percent of that.  What bounds it now is vector arithmetic and LDS in about
 // equal parts; its traffic (X once each way) runs at 2.5 TB/s.
 // LDS: (twiddles W_{2m}) + 3 G lines of B rows of 2A (+1) values.
 // ---------------------------------------------------------------------------
@@ -1633,18 +1635,18 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 }
 
 // ---------------------------------------------------------------------------
-// k_convh: the FP64 convolution of 3 or 4 layers at the y lengths whose lines
-// of both halves k_convz can't hold (192 with 4 layers, and 256): one half of
+// k_convh: the FP64 convolution of 4 layers at the y lengths whose lines of
+// both halves k_convz can't hold (192 and 256; 3 layers fit there): one half of
 // the padded y spectrum after the other, as k_conv (half 1 is added onto what
 // half 0 left in X'), its passes spread over all threads as in k_convz.
 // Bound by latency at two wavefronts to a SIMD (256 VGPRs, a slice's lines of
 // one half in up to 59 KiB of LDS): passes of one item per thread keep a few
 // values each and have no line groups half of which idle, where k_conv's
-// wavefronts hold 16 values a lane for whole lines.  Images of 250x250x3,
-// 20 of them: 208 us against 370; 256x256x4, 32: 477 against 638; 180x180x4,
-// 20: 171 against 197.  With 8 padded layers (112 KiB: one workgroup of 512 to
-// a CU, only half of whose threads hold a z column) 256x256x8, 48 took 2554 us
-// against 1687, 180x180x8, 20 582 against 568: k_conv keeps those.
+// wavefronts hold 16 values a lane for whole lines.  Us a launch, k_conv ->
+// k_convh: 256 x 256 x 4, 32 images 638 -> 477; 180 x 180 x 4, 20 images 197 -> 171.
+// With 8 padded layers (112 KiB: one workgroup of 512 to a CU, only half of
+// whose threads hold a z column) 256 x 256 x 8, 48 images took 2554 against 1687
+// and 180 x 180 x 8, 20 images 582 against 568: k_conv keeps those.
 // LDS: twiddles W_{2m} + 3 nz lines of B rows of A (+1) values.
 // ---------------------------------------------------------------------------
 template <int MZ, int BUILD>
