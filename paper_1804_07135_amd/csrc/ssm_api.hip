@@ -173,6 +173,21 @@ int convz_gmax(const Prob& p, size_t tsize)
     return g;
 }
 
+// Whether a problem that k_convz can take goes to k_conv, X' apart from X: 5
+// and 6 layers of 256 points (FP32), where k_conv's three workgroups to a CU are
+// faster than k_convz's two.  Us a launch, k_convz -> k_conv: 250 x 250 x 5, 4
+// images 60.0 -> 52.9, 60 images 596 -> 576; 100 x 250 x 5, 20 images 111 -> 99; 250 x
+// 250 x 6, 30 images 397 -> 375.  But not 5 layers of a batch whose x half-spectra
+// X (x_bytes) nearly fill the 256 MiB last-level cache with X' beside them: the x
+// kernels then lose more.  An iteration, us, by X's MiB: 103 301.5 -> 299.8, 118
+// 337.5 -> 344.2, 132 381 -> 390, 162 479 -> 483, 176 520.5 -> 518.6, 191 581 -> 566
+// (6 layers: 124 374.4 -> 375.7, 159 493 -> 492, 194 612 -> 592).
+bool conv_apart(const Prob& p, long long x_bytes)
+{
+    return p.conv1 == 2 && p.mz == 8 && conv_build(p.mz, p.lmy, p.f3y) == 8 &&
+           !(p.nz == 5 && x_bytes >= 110LL << 20 && x_bytes < 170LL << 20);
+}
+
 size_t lds_convg(const Prob& p, int G, size_t tsize)
 {
     const int build = conv_build(p.mz, p.lmy, p.f3y);
@@ -319,8 +334,9 @@ int conv_wgs(const Prob& p)
     return (w + 7) / 8 * 8;
 }
 
+// compact: every problem that can be convolved in place, whatever is faster
 ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::vector<Tiles>* tiles,
-                      Plan& pl, std::string& err)
+                      Plan& pl, std::string& err, bool compact = false)
 {
     const bool rk = (prec_flags & SSM_WITH_RK) != 0;
     const int prec = prec_flags & ~SSM_WITH_RK;
@@ -335,7 +351,7 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
     pl.geo.resize(np);
     std::map<std::tuple<int, int, int>, int> shape_id;
     long long img = 0, spin = 0, xo = 0, xpo = 0, ep = 0, ap = 0, fp = 0, fm = 0;
-    long long batch_rows = 0, batch_slices = 0;
+    long long batch_rows = 0, batch_slices = 0, x_bytes = 0;
     // SSM_LEN3_CT_X / _Y: precisions (bit 0 FP32-mixed, bit 1 FP64) in
     // which a compile-time 3 2^a length is preferred to a compile-time power
     // of two
@@ -348,6 +364,7 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         int mx, lg, f3;
         transform_len(pr[i].nx, x_fast, mx, lg, f3);
         batch_slices += (long long)pr[i].n_images * (mx + 1);
+        x_bytes += (long long)pr[i].n_images * (mx + 1) * 3 * pr[i].nz * pr[i].ny * 2 * pl.tsize;
     }
     for (int i = 0; i < np; ++i) {
         const ssm_problem& q = pr[i];
@@ -363,6 +380,7 @@ ssm_status build_plan(const ssm_problem* pr, int np, int prec_flags, const std::
         p.nhz = q.nz > 1 ? 2 : 1;
         p.N = (long long)q.nx * q.ny * q.nz;
         p.conv1 = conv_inplace(p.nz, p.mz, conv_build(p.mz, p.lmy, p.f3y), (int)pl.tsize);
+        if (!compact && conv_apart(p, x_bytes)) p.conv1 = 0;
         const Tiles t = tiles ? (*tiles)[i] : default_tiles(p, pl.tsize, batch_rows, batch_slices);
         apply_tiles(p, t, pl.tsize);
         pl.tiles.push_back(t);
@@ -1762,6 +1780,11 @@ ssm_status ssm_eval_noalloc(const ssm_problem* p, int32_t n_problems, int32_t pr
         ssm_status s = build_plan(p, n_problems, precision, nullptr, pl, err);
         if (s != SSM_OK) return fail(nullptr, s, err);
         carve_static(pl);
+        if (pl.total > kStaticScratchBytes) {
+            s = build_plan(p, n_problems, precision, nullptr, pl, err, true);
+            if (s != SSM_OK) return fail(nullptr, s, err);
+            carve_static(pl);
+        }
         if (pl.total > kStaticScratchBytes)
             return fail(nullptr, SSM_EUNSUPPORTED,
                         "ssm_eval_noalloc: these problems need " + std::to_string(pl.total) +

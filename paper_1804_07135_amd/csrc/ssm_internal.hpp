@@ -108,25 +108,19 @@ __host__ __device__ constexpr size_t convh_lds(int build, int nz)
     return (size_t)(2 * c.A * c.B + 3 * nz * convh_line(c)) * 16;
 }
 
-// Whether the in-place kernels take a problem: monolayers always (of the
+// Whether the in-place kernels can take a problem: monolayers always (of the
 // lengths with a build); several layers where one slice's lines of both halves
 // fit kConvzLds, two workgroups to a CU; one to a CU would hold fewer wavefronts
-// than k_conv's three (256 x 256 x 8) or, in FP64, not fit.  But not 5 and 6 layers
-// of 256 points (FP32), where k_conv is the faster with its three workgroups
-// (us a launch, k_convz -> k_conv: 250 x 250 x 5, 20 images 206 -> 201, 100 x 250
-// x 5, 20 images 111 -> 99, 250 x 250 x 6, 30 images 396 -> 375; an iteration is 1 to
-// 7% shorter with it, but 3% longer for 250 x 250 x 5, 20 images, whose X fits the
-// last-level cache by itself but not with X').  3 layers of
-// 256 points in FP64 go the other way (250 x 250 x 3, 20 images: k_convz 208,
-// k_convh 273, k_conv 377; of 192 points, 180 x 180 x 3, 20 images: 112, 147, 172).
-// (_all, _min: every layer count, the smallest one, of a padded count mz.)
+// than k_conv's three (256 x 256 x 8) or, in FP64, not fit.  3 layers of 192 and 256
+// points in FP64 fit and are the faster there (us a launch, k_convz, k_convh,
+// k_conv: 250 x 250 x 3, 20 images 208, 273, 377; 180 x 180 x 3, 20 images 112, 147,
+// 172).  5 and 6 layers of 256 points in FP32 fit and aren't: the plan decides
+// (conv_apart).  (_all, _min: every layer count, the smallest one, of a padded
+// count mz.)
 constexpr size_t kConvzLds = 80 * 1024;
 __host__ __device__ constexpr int conv_inplace(int nz, int mz, int build, int tsize)
 {
-    return build == 0 || mz > 8 || (mz == 8 && build == 8) ? 0
-           : mz == 1                                          ? 1
-           : convz_lds(build, 1, nz, tsize) <= kConvzLds      ? 2
-                                                              : 0;
+    return build == 0 || mz > 8 ? 0 : mz == 1 ? 1 : convz_lds(build, 1, nz, tsize) <= kConvzLds ? 2 : 0;
 }
 __host__ __device__ constexpr bool conv_inplace_all(int mz, int build, int tsize) { return conv_inplace(mz, mz, build, tsize) != 0; }
 __host__ __device__ constexpr bool conv_inplace_min(int mz, int build, int tsize)

@@ -518,7 +518,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 // result goes to the output slice and the y half 1 result is added onto it
 // (each thread adds onto the values it stored itself).  The kernel
 // spectrum carries 1/(Px Py Pz).
-// Serves what the kernels below don't: 5 to 8 layers where conv_inplace says so,
+// Serves what the kernels below don't: 5 to 8 layers at the longer y lengths,
 // 9 to 16 layers, and y lengths without a compile-time build.
 // LDS: twiddles (2 m_y) + G*3*nz lines of m_y.
 // ---------------------------------------------------------------------------
@@ -1601,8 +1601,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     // z-phase: item (slice, half, frequency)
     for (int it = threadIdx.x; it < G * 2 * MY; it += kNT) {
         const int gh = it / MY, f = it - gh * MY, hy = gh & 1, r = f / A, q = f - r * A;
-        conv_zcolumn<T, MZ, LMY, F3, true, MZ == 8>(p, kx, hy, f, lines + (gh >> 1) * L * LS + r * JS + hy * A + q,
-                                                    LS, nhat, tw);
+        conv_zcolumn<T, MZ, LMY, F3, true, (MZ == 8 && MY < 256)>(
+            p, kx, hy, f, lines + (gh >> 1) * L * LS + r * JS + hy * A + q, LS, nhat, tw);
     }
     __syncthreads();
 
